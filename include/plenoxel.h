@@ -555,23 +555,23 @@ int64_t plx_scene_table_bytes(int32_t n_scenes);
 int plx_scene_table_set(const plx_grid *scenes, int32_t n_scenes, void *table, int64_t table_bytes,
                         plx_stream stream);
 
-/* Bytes of the tile queue of plx_render_views: device memory, 256-byte
- * aligned, zero-filled once before its first use (every launch leaves it at
- * zero again, apart from the sticky status word). */
+/* Bytes of the queue buffer of plx_render_views: device memory, 256-byte
+ * aligned, zero-filled once before its first use.  It holds the sticky status
+ * word of the launches that were given it. */
 #define PLX_VIEWS_QUEUE_BYTES 256
 
 /* Renders a batch of novel views of resident scenes (the forward model of
  * plx_render_fwd, Sec. 3.1-3.3, with rays generated on the device;
  * interactive rendering is claimed in Sec. 1).  The views may mix scenes and
- * resolutions.  All pixels of all views form one queue of 16x16-pixel tiles
- * drained by a persistent grid, so the colour of a pixel depends only on its
- * ray and scene, never on the rest of the batch.  scene_table: written by
+ * resolutions.  All pixels of all views of a launch form one list of small
+ * tiles, one wave each; the colour of a pixel depends only on its view and
+ * scene, never on the rest of the batch.  scene_table: written by
  * plx_scene_table_set for n_scenes scenes of storage type sh_dtype.  views:
  * host array, validated here (scene index, size, focal, offset) and passed
  * to the device as kernel arguments, 24 views per launch: the call
  * allocates nothing, copies nothing through a copy engine, never
- * synchronises, and the array may be released on return.  queue: the tile
- * queue (PLX_VIEWS_QUEUE_BYTES); launches that share one must be ordered on
+ * synchronises, and the array may be released on return.  queue: the queue
+ * buffer (PLX_VIEWS_QUEUE_BYTES); launches that share one must be ordered on
  * a stream, launches on separate queues may overlap.  A table that is not of
  * sh_dtype (or holds fewer scenes than a view names) renders nothing for
  * those views and sets the queue's status word, which

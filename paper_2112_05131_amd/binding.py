@@ -658,7 +658,7 @@ VIEWS_QUEUE_BYTES = 256
 
 
 def views_queue(device=None) -> torch.Tensor:
-    """A tile queue for plx_render_views (zero-filled, as the call needs)."""
+    """A queue buffer for plx_render_views (zero-filled, as the call needs)."""
     return torch.zeros(VIEWS_QUEUE_BYTES, dtype=torch.uint8, device=device if device is not None else "cuda")
 
 

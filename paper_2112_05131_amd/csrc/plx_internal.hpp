@@ -58,6 +58,9 @@ struct GridDev {
     const uint32_t *occ;     // cell bitmap
     const uint8_t *bdist;    // brick distances
     int64_t n_vox;
+    // bytes of the index and of the records when both fit 32-bit offsets
+    // (then buffer loads reach them), else 0
+    uint32_t index_bytes, data_bytes;
 };
 
 inline GridDev to_dev(const plx_grid *g) {
@@ -79,6 +82,12 @@ inline GridDev to_dev(const plx_grid *g) {
     d.bdist = g->occ ? reinterpret_cast<const uint8_t *>(g->occ) + occ_brick_offset(g->reso)
                      : nullptr;
     d.n_vox = g->n_vox;
+    // a NULL id times the record size wraps to the last record below 4 GiB
+    constexpr int64_t kLimit = 0xffffff00ll;
+    const int64_t ib = n_cells(g->reso) * 4, db = g->n_vox * (g->sh_dtype == PLX_F32 ? 128 : 64);
+    const bool fits = ib <= kLimit && db <= kLimit;
+    d.index_bytes = fits ? (uint32_t)ib : 0u;
+    d.data_bytes = fits ? (uint32_t)db : 0u;
     return d;
 }
 

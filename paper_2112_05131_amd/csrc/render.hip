@@ -56,17 +56,15 @@
 #include <mutex>
 #include <vector>
 
-#include "plx_internal.hpp"
+#include "march.hpp"
 
 namespace plx {
 namespace {
 
-constexpr int kWave = 64;
 constexpr int kThreads = 256;          // rays per block
 constexpr int kWavesPerBlock = kThreads / kWave;
 constexpr int kChunk = 16;             // candidate samples tested per round
 constexpr int kQCap = 8 * kWave;       // queue entries per wave (8 corners per lane per step)
-constexpr float kSkipMargin = 0.05f;   // in steps
 
 enum { MODE_FWD = 0, MODE_BWD = 1, MODE_TRAIN = 2, MODE_MAXW = 3 };
 
@@ -78,13 +76,6 @@ struct Priors {
     float eps;         // beta epsilon
     double *loss;      // [2] (L_s, L_b) ADDED, or NULL
 };
-
-// Background colour of a ray: its own when the call gives one per ray.
-__device__ __forceinline__ void ray_background(const float *bg_rgb, const float bg[3], int64_t ray,
-                                               float out[3]) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) out[c] = bg_rgb ? bg_rgb[3 * ray + c] : bg[c];
-}
 
 // Beta prior of one ray from its optical depth tau (FP64; 1 - T = -expm1(-tau)
 // stays accurate for a nearly empty ray): returns dL_b/dsigma_k / delta_k =
@@ -144,8 +135,6 @@ struct RenderArgs {
     int nb8;
 };
 
-__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
-
 // Wave-uniform copies (readfirstlane) of values the compiler cannot prove
 // uniform, so that they live in scalar registers.
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -179,6 +168,8 @@ __device__ inline GridDev uniform_grid(const GridDev &s) {
     g.occ = uni_ptr(s.occ);
     g.bdist = uni_ptr(s.bdist);
     g.n_vox = uni64(s.n_vox);
+    g.index_bytes = (uint32_t)uni((int)s.index_bytes);
+    g.data_bytes = (uint32_t)uni((int)s.data_bytes);
     return g;
 }
 
@@ -276,11 +267,6 @@ struct Queue {
     float4 *v;      // [kQCap] accumulated density, R, G, B gradients
     float *y;       // [64][9] SH basis of each lane's ray
 };
-
-__device__ __forceinline__ int lanes_below(uint64_t m) {
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
 
 // Appends, for every active lane, its corners in `mask` (bit c = corner c)
 // that are not NULL, with their accumulators.  One offset reservation per
@@ -503,42 +489,6 @@ __device__ __forceinline__ uint32_t chunk_bits(const GridDev &g, const RayGeom &
     return m & valid;
 }
 
-// Number of further samples after sample k (in the direction of travel)
-// that certainly stay inside the box of bricks within R of brick b, where
-// sample k lies (at t = t_near + k*step): the box's exit parameter along the
-// ray, less a margin of 5% of a step.
-// Both walks over a ray's bricks (counting and emitting its segments) must
-// cut identical segments, so this runs without FMA contraction like the
-// sample recipe itself.
-template <bool FORWARD>
-__device__ __forceinline__ int samples_in_box(const GridDev &g, const RayGeom &r, int k,
-                                              const int b[3], int R) {
-#pragma clang fp contract(off)
-    const int nb[3] = {g.bx, g.by, g.bz};
-    const float t = r.t_near + (float)k * g.step;
-    float t_edge = FORWARD ? __builtin_inff() : -__builtin_inff();
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const float dg = r.dg[a];
-        if (dg == 0.0f) continue;
-        // box faces on the grid boundary are never crossed by a sample
-        const bool up = (dg > 0.0f) == FORWARD;
-        const int bf = up ? b[a] + R : b[a] - R;
-        if (up ? bf >= nb[a] - 1 : bf <= 0) continue;
-        const float face = (float)((up ? bf + 1 : bf) * PLX_BRICK);
-        const float tf = (face - r.og[a]) / dg;
-        t_edge = FORWARD ? fminf(t_edge, tf) : fmaxf(t_edge, tf);
-    }
-    const float span = FORWARD ? (t_edge - t) : (t - t_edge);
-    float q = span / g.step - kSkipMargin;
-    q = q < (float)kMaxSamples ? q : (float)kMaxSamples;
-    return q > 0.0f ? (int)q : 0;
-}
-
-__device__ __forceinline__ int64_t brick_id(const GridDev &g, const int b[3]) {
-    return ((int64_t)b[0] * g.by + b[1]) * g.bz + b[2];
-}
-
 // Brick-level skip.  Returns the distance D of the brick of sample k (0 when
 // it has an occupied cell); for D > 0 also the number of further samples m
 // (in the direction of travel) that certainly stay in the empty box of bricks
@@ -601,14 +551,13 @@ __device__ __forceinline__ int next_backward(const GridDev &g, const RayGeom &r,
 // ------------------------------------------------------------ forward march
 
 // Front-to-back march of one ray (Eq. (1)).  Returns the colour before the
-// background is added in C and the optical depth in tau.  With STORE, the
-// first `cap` occupied samples (index and pre-activation values) go to
-// kidx/vals and their total count to *count.
-template <int DT, bool STORE = false>
+// background is added in C and the optical depth in tau.  The first `cap`
+// occupied samples (index and pre-activation values) go to kidx/vals and their
+// total count to *count.
+template <int DT>
 __device__ __forceinline__ void march_forward(const GridDev &g, const RayGeom &r, int n,
                                               const float y[9], CornerCache &cc, float C[3],
-                                              double &tau, int *count = nullptr, int *kidx = nullptr,
-                                              float4 *vals = nullptr, int cap = 0) {
+                                              double &tau, int *count, int *kidx, float4 *vals, int cap) {
     C[0] = C[1] = C[2] = 0.0f;
     tau = 0.0;
     Cursor cur{0, 0, 0u};
@@ -623,13 +572,11 @@ __device__ __forceinline__ void march_forward(const GridDev &g, const RayGeom &r
         float w[8];
         corner_weights(s.f, w);
         const Q4 v = interpolate(cc, w);
-        if (STORE) {
-            if (stored < cap) {
-                kidx[stored] = k;
-                vals[stored] = make_float4(v.s, v.r, v.g, v.b);
-            }
-            ++stored;
+        if (stored < cap) {
+            kidx[stored] = k;
+            vals[stored] = make_float4(v.s, v.r, v.g, v.b);
         }
+        ++stored;
         const float sd = fmaxf(v.s, 0.0f) * s.delta;
         const float wk = expf(-(float)tau) * (-expm1f(-sd));
         C[0] += wk * fmaxf(v.r, 0.0f);
@@ -637,17 +584,12 @@ __device__ __forceinline__ void march_forward(const GridDev &g, const RayGeom &r
         C[2] += wk * fmaxf(v.b, 0.0f);
         tau += (double)sd;
     }
-    if (STORE) *count = stored;
-}
-
-__device__ inline void sh_basis_all(const float d[3], float y[9]) {
-#pragma unroll
-    for (int l = 0; l < 9; ++l) y[l] = sh_basis_at(l, d[0], d[1], d[2]);
+    *count = stored;
 }
 
 // ------------------------------------------------------------------ kernels
 
-template <int DT, bool STORE>
+template <int DT>
 __global__ __launch_bounds__(kThreads) void render_fwd_kernel(GridDev g, RenderArgs a) {
     const int blk = xcd_logical_block(blockIdx.x, a.nb8);
     if (blk >= a.n_blocks) return;
@@ -667,13 +609,8 @@ __global__ __launch_bounds__(kThreads) void render_fwd_kernel(GridDev g, RenderA
     cc.cell[0] = cc.cell[1] = cc.cell[2] = -1;
     float C[3];
     double tau;
-    if (STORE) {
-        const int64_t base = ray * a.st_cap;
-        march_forward<DT, true>(g, r, n, y, cc, C, tau, a.st_count + ray,
-                                a.st_kidx + base, a.st_vals + base, a.st_cap);
-    } else {
-        march_forward<DT>(g, r, n, y, cc, C, tau);
-    }
+    const int64_t base = ray * a.st_cap;
+    march_forward<DT>(g, r, n, y, cc, C, tau, a.st_count + ray, a.st_kidx + base, a.st_vals + base, a.st_cap);
     const float T_final = expf(-(float)tau);
     float bgc[3];
     ray_background(a.bg_rgb, a.bg, ray, bgc);
@@ -683,12 +620,12 @@ __global__ __launch_bounds__(kThreads) void render_fwd_kernel(GridDev g, RenderA
 }
 
 // Ray-order backward of the stored-state call.  Every lane of a block stays
-// until its wave is done (the queue drains need all 64 lanes).  With STATE,
-// a ray whose occupied samples were all stored by the forward pass replays
+// until its wave is done (the queue drains need all 64 lanes).  A
+// ray whose occupied samples were all stored by the forward pass replays
 // them from the state (index loads only, no record gathers or
 // interpolation); a ray with more than st_cap samples replays by traversal
 // and recomputation.
-template <int DT, bool STATE>
+template <int DT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3)))
 void render_bwd_kernel(GridDev g, RenderArgs a) {
     __shared__ int q_count[kWavesPerBlock];
@@ -763,11 +700,11 @@ void render_bwd_kernel(GridDev g, RenderArgs a) {
     // nothing accumulated yet, which is what the backward expects
     Cursor cur{k_hi, 0, 0u};
     bool active = live && n > 0 && k_lo <= k_hi;
-    // stored samples of this ray (STATE): replayed from index j down to 0
+    // stored samples of this ray: replayed from index j down to 0
     bool stored = false;
     int j = -1;
     int64_t st_base = 0;
-    if (STATE && live) {
+    if (live) {
         const int cnt = a.st_count[ray];
         stored = cnt <= a.st_cap;
         j = cnt - 1;
@@ -778,7 +715,7 @@ void render_bwd_kernel(GridDev g, RenderArgs a) {
         if (active) {
             int k;
             Q4 vs = q4_zero();
-            if (STATE && stored) {
+            if (stored) {
                 k = -1;
                 if (j >= 0) {
                     k = a.st_kidx[st_base + j];
@@ -794,10 +731,10 @@ void render_bwd_kernel(GridDev g, RenderArgs a) {
                 active = false;
             } else {
                 const Sample s = sample_at(g, r, k);
-                move_to<DT, true>(g, cc, s.cell, acc, qu, y, !(STATE && stored));
+                move_to<DT, true>(g, cc, s.cell, acc, qu, y, !stored);
                 float w[8];
                 corner_weights(s.f, w);
-                const Q4 v = (STATE && stored) ? vs : interpolate(cc, w);
+                const Q4 v = stored ? vs : interpolate(cc, w);
                 const float sd = fmaxf(v.s, 0.0f) * s.delta;
                 const double tau_before = fmax(tau_after - (double)sd, 0.0);
                 const float T_before = expf(-(float)tau_before);
@@ -2468,7 +2405,36 @@ __device__ inline void camera_ray(const plx_view &v, int px, int py, float o[3],
     }
 }
 
-constexpr int kTileW = 16, kTileH = 16;  // pixels per tile = rays per block
+// How a view is cut: a workgroup is one wave and marches kW x kH pixels, P
+// lanes each.  One wave per workgroup and one workgroup per tile let the
+// dispatcher even out tiles of very different cost (with four waves and 256
+// pixels per workgroup and a queue of tiles, an 800x800 view of a 512^3 scene
+// had 18% of its wave slots filled on average).  Many lanes a ray shorten the
+// chain of rounds of a view that does not fill the chip, few lanes share a
+// wave's set-up among more rays.  Measured with 16 / 8 / 4 lanes (ms, FP16
+// records): 200x200 on 512^3 0.15 / 0.25 / 0.56, 400x400 on 512^3 0.24 / 0.32 /
+// 0.65, 800x800 on 512^3 0.70 / 0.66 / 0.72, 1280x720 on 256^3 0.90 / 0.76 /
+// 0.70, 1920x1080 on 256^3 1.81 / 1.50 / 1.26.  From 256x256 pixels on 16
+// lanes fill the chip alone, and 8 leave room for another stream's launch
+// (two 288x288 views on two streams: 0.49 ms together, 0.67 one after the
+// other).  The choice follows the view, not its launch: the order of a ray's
+// additions depends on the cut, and a view has the same bits whatever it is
+// batched with.
+template <int P_> struct ViewsCut {
+    static constexpr int P = P_, M = 4;
+    static constexpr int kW = P == 16 ? 2 : 4, kH = kWave / P / kW;
+};
+inline int view_lanes(const plx_view &v) {
+    const int64_t n = (int64_t)v.width * v.height;
+    return n < (1 << 16) ? 16 : (n < (3 << 18) ? 8 : 4);
+}
+// Tiles of a view (host), by its lanes per ray.
+template <class CUT> inline int64_t tiles_of(const plx_view &v) {
+    return (int64_t)((v.width + CUT::kW - 1) / CUT::kW) * ((v.height + CUT::kH - 1) / CUT::kH);
+}
+// Workgroups of a launch; beyond it (16.7M pixels) they stride over the tiles
+// (a grid holds fewer than 2^32 threads, a view may have 2^32 pixels).
+constexpr int64_t kViewsMaxBlocks = 1 << 20;
 
 // Scene table (device, written by plx_scene_table_set): a 256-byte header,
 // then one GridDev per scene.
@@ -2485,13 +2451,10 @@ constexpr int64_t kSceneTableHead = 256;
 // to kViewsPerLaunch views, and a longer list is split into several.
 constexpr int kViewsPerLaunch = 24;
 
-// The caller's tile queue (PLX_VIEWS_QUEUE_BYTES, zero before first use):
-// the next tile, the blocks that have left, and a sticky status word.  The
-// last block of a launch to leave resets the first two, so every launch
-// finds the queue at zero without a memset.
+// The caller's queue buffer (PLX_VIEWS_QUEUE_BYTES, zero before first use)
+// holds a sticky status word; the dispatcher hands out the tiles.
 struct ViewsQueue {
-    unsigned long long next;
-    unsigned done;
+    unsigned reserved[3];
     unsigned status;
 };
 
@@ -2500,8 +2463,9 @@ struct ViewsArgs {
     const GridDev *scenes;
     plx_view v[kViewsPerLaunch];
     int64_t tile_start[kViewsPerLaunch + 1];
+    int lanes[kViewsPerLaunch];  // per ray (view_lanes)
     int n_views;
-    ViewsQueue *queue;
+    unsigned *status;
     float bg[3];
     float *rgb_out;
 };
@@ -2526,69 +2490,60 @@ __global__ void scene_setup_kernel(SceneSetupArgs a) {
     }
 }
 
-// Persistent tile queue over all pixels of all views of the launch: each
-// block takes the next 16x16-pixel tile, finds its view, generates the rays
-// of its pixels (one per lane) and runs the same forward march as
-// plx_render_fwd.  A pixel's colour depends only on its own ray and scene,
-// never on the rest of the batch.
+// One tile of a view: the wave generates the rays of its pixels and marches
+// them.
+template <int DT, class CUT>
+__device__ __forceinline__ void render_tile(const GridDev &g, const plx_view &v, int64_t tile, const float bg[3],
+                                            float *rgb_out, void *lds) {
+    constexpr int P = CUT::P, M = CUT::M;
+    MarchLds<P, M> &sh = *static_cast<MarchLds<P, M> *>(lds);
+    const int tpr = (v.width + CUT::kW - 1) / CUT::kW;
+    const int slot = lane_id() / P;
+    const int px = (int)(tile % tpr) * CUT::kW + slot % CUT::kW;
+    const int py = (int)(tile / tpr) * CUT::kH + slot / CUT::kW;
+    const bool in = px < v.width && py < v.height;
+    float o[3], d[3];
+    camera_ray(v, min(px, v.width - 1), min(py, v.height - 1), o, d);
+    RayGeom r;
+    const int n = in ? ray_setup(g, o, d, r) : 0;
+    march_basis(sh, d);
+    float C[3];
+    double tau;
+    march_rays<DT>(g, sh, r, n, C, tau);
+    if (in && lane_id() % P == 0) {
+        const float T_final = expf(-(float)tau);
+        float *out = rgb_out + 3 * (v.out_offset + (int64_t)py * v.width + px);
+#pragma unroll
+        for (int c3 = 0; c3 < 3; ++c3) out[c3] = C[c3] + T_final * bg[c3];
+    }
+}
+
+// Novel views, a tile per workgroup (one wave).
 template <int DT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void views_kernel(ViewsArgs a) {
-    __shared__ long long tile_sh;
+    constexpr size_t kLds = sizeof(MarchLds<4, ViewsCut<4>::M>);  // the largest of the cuts
+    __shared__ __align__(16) unsigned char lds[kLds];
     // a table of other scenes' storage type (or not a scene table): nothing
     // is rendered and the status word says so
-    const unsigned magic = a.table->magic;
-    const int n_scenes = a.table->n_scenes, table_dt = a.table->sh_dtype;
-    const bool ok = magic == kSceneMagic && table_dt == DT;
-    if (!ok && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&a.queue->status, 1u);
-    const int64_t n_tiles = ok ? a.tile_start[a.n_views] : 0;
-    while (n_tiles > 0) {
-        if (threadIdx.x == 0) tile_sh = (long long)atomicAdd(&a.queue->next, 1ull);
-        __syncthreads();
-        const int64_t tile = uni64(tile_sh);
-        __syncthreads();
-        if (tile >= n_tiles) break;
+    const bool ok = a.table->magic == kSceneMagic && a.table->sh_dtype == DT;
+    for (int64_t tile = blockIdx.x; tile < a.tile_start[a.n_views]; tile += gridDim.x) {
         int lo = 0;  // the view of the tile
         for (int i = 1; i < a.n_views; ++i)
             if (a.tile_start[i] <= tile) lo = i;
         const plx_view &v = a.v[lo];
-        const int width = uni(v.width), height = uni(v.height);
-        const int64_t tl = tile - a.tile_start[lo];
-        const int tpr = (width + kTileW - 1) / kTileW;
-        const int px = (int)(tl % tpr) * kTileW + (int)(threadIdx.x % kTileW);
-        const int py = (int)(tl / tpr) * kTileH + (int)(threadIdx.x / kTileW);
-        const int scene = uni(v.scene);
-        if (scene >= n_scenes) {
-            if (threadIdx.x == 0) atomicOr(&a.queue->status, 1u);
+        if (!ok || v.scene >= a.table->n_scenes) {
+            if (threadIdx.x == 0) atomicOr(a.status, 1u);
             continue;
         }
-        if (px < width && py < height) {
-            const GridDev g = uniform_grid(a.scenes[scene]);
-            float o[3], d[3];
-            camera_ray(v, px, py, o, d);
-            RayGeom r;
-            const int n = ray_setup(g, o, d, r);
-            float y[9];
-            sh_basis_all(d, y);
-            CornerCache cc;
-            cc.cell[0] = cc.cell[1] = cc.cell[2] = -1;
-            float C[3];
-            double tau;
-            march_forward<DT>(g, r, n, y, cc, C, tau);
-            const float T_final = expf(-(float)tau);
-            float *out = a.rgb_out + 3 * (uni64(v.out_offset) + (int64_t)py * width + px);
-#pragma unroll
-            for (int c3 = 0; c3 < 3; ++c3) out[c3] = C[c3] + T_final * a.bg[c3];
-        }
-    }
-    // leave; the last block resets the queue for the next launch (every
-    // block's last take from it precedes its leaving)
-    if (threadIdx.x == 0) {
-        __threadfence();
-        if (atomicAdd(&a.queue->done, 1u) == gridDim.x - 1) {
-            atomicExch(&a.queue->next, 0ull);
-            atomicExch(&a.queue->done, 0u);
-        }
+        const GridDev g = uniform_grid(a.scenes[v.scene]);
+        const int64_t tl = tile - a.tile_start[lo];
+        if (a.lanes[lo] == 16)
+            render_tile<DT, ViewsCut<16>>(g, v, tl, a.bg, a.rgb_out, lds);
+        else if (a.lanes[lo] == 8)
+            render_tile<DT, ViewsCut<8>>(g, v, tl, a.bg, a.rgb_out, lds);
+        else
+            render_tile<DT, ViewsCut<4>>(g, v, tl, a.bg, a.rgb_out, lds);
     }
 }
 
@@ -2639,7 +2594,7 @@ int validate_rays(const float *o, const float *d, int64_t n, const char *fn) {
     return PLX_OK;
 }
 
-template <int MODE, bool STATE = false>
+template <int MODE>
 int launch_render(const plx_grid *grid, RenderArgs &a, hipStream_t s, const char *fn) {
     const int64_t nb = (a.n_rays + kThreads - 1) / kThreads;
     if (nb > 0x7ffffff0) return fail(PLX_EINVAL, "%s: too many rays", fn);
@@ -2648,10 +2603,10 @@ int launch_render(const plx_grid *grid, RenderArgs &a, hipStream_t s, const char
     GridDev g = to_dev(grid);
     if constexpr (MODE == MODE_FWD) {
         PLX_DISPATCH_DT(grid->sh_dtype, DT,
-                        render_fwd_kernel<DT, STATE><<<a.nb8, kThreads, 0, s>>>(g, a));
+                        render_fwd_kernel<DT><<<a.nb8, kThreads, 0, s>>>(g, a));
     } else {
         static_assert(MODE == MODE_BWD, "the ray-order backward serves plx_render_bwd_state");
-        PLX_DISPATCH_DT(grid->sh_dtype, DT, render_bwd_kernel<DT, STATE><<<a.nb8, kThreads, 0, s>>>(g, a));
+        PLX_DISPATCH_DT(grid->sh_dtype, DT, render_bwd_kernel<DT><<<a.nb8, kThreads, 0, s>>>(g, a));
     }
     return check_launch(fn);
 }
@@ -3313,7 +3268,7 @@ int plx_render_fwd_state(const plx_grid *grid, const plx_render_opts *opts, cons
     if ((rc = attach_state(a, state, state_bytes, cap, fn))) return rc;
     a.rgb_out = rgb_out;
     a.tau_out = tau_out;
-    return launch_render<MODE_FWD, true>(grid, a, as_stream(stream), fn);
+    return launch_render<MODE_FWD>(grid, a, as_stream(stream), fn);
 }
 
 int plx_render_bwd_state(const plx_grid *grid, const plx_render_opts *opts, const float *rays_o,
@@ -3334,7 +3289,7 @@ int plx_render_bwd_state(const plx_grid *grid, const plx_render_opts *opts, cons
     a.tau_in = tau_fwd;
     a.grad = grad;
     a.touched = touched;
-    return launch_render<MODE_BWD, true>(grid, a, as_stream(stream), fn);
+    return launch_render<MODE_BWD>(grid, a, as_stream(stream), fn);
 }
 
 int64_t plx_scene_table_bytes(int32_t n_scenes) {
@@ -3399,7 +3354,7 @@ int plx_render_views(const void *scene_table, int32_t n_scenes, int32_t sh_dtype
     ViewsArgs va;
     va.table = static_cast<const SceneTableHeader *>(scene_table);
     va.scenes = reinterpret_cast<const GridDev *>(static_cast<const char *>(scene_table) + kSceneTableHead);
-    va.queue = static_cast<ViewsQueue *>(queue);
+    va.status = &static_cast<ViewsQueue *>(queue)->status;
     va.rgb_out = rgb_out;
     for (int i = 0; i < 3; ++i) va.bg[i] = opts->background[i];
     for (int32_t first = 0; first < n_views; first += kViewsPerLaunch) {
@@ -3408,12 +3363,14 @@ int plx_render_views(const void *scene_table, int32_t n_scenes, int32_t sh_dtype
         for (int i = 0; i < va.n_views; ++i) {
             const plx_view &v = views[first + i];
             va.v[i] = v;
+            va.lanes[i] = view_lanes(v);
             va.tile_start[i] = tiles;
-            tiles += (int64_t)((v.width + kTileW - 1) / kTileW) * ((v.height + kTileH - 1) / kTileH);
+            tiles += va.lanes[i] == 16 ? tiles_of<ViewsCut<16>>(v)
+                                       : (va.lanes[i] == 8 ? tiles_of<ViewsCut<8>>(v) : tiles_of<ViewsCut<4>>(v));
         }
         va.tile_start[va.n_views] = tiles;
-        const int64_t nblk = tiles < 2048 ? tiles : 2048;  // persistent: 8 blocks per CU
-        PLX_DISPATCH_DT(sh_dtype, DT, views_kernel<DT><<<(unsigned)nblk, kThreads, 0, s>>>(va));
+        const unsigned nblk = (unsigned)std::min(tiles, kViewsMaxBlocks);
+        PLX_DISPATCH_DT(sh_dtype, DT, views_kernel<DT><<<nblk, kWave, 0, s>>>(va));
         int rc = check_launch(fn);
         if (rc) return rc;
     }

@@ -4,7 +4,7 @@ Scenes (Grid objects, one SH storage type) stay resident on the device.
 Requests (scene, camera pose, focal length, width, height) arrive at any time
 and wait in a FIFO queue.  Whenever a stream of the pool is idle, every queued
 request that fits the HBM admission budget joins one batch, which is rendered
-by a single persistent launch of plx_render_views on that stream.  A batch
+by a single launch of plx_render_views on that stream.  A batch
 never waits for earlier batches: requests that arrive while others are on the
 device are admitted as streams and budget free up, and their work overlaps with
 the running launches.  Completion is observed through a per-batch event;

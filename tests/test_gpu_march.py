@@ -1,0 +1,158 @@
+"""GPU tests of the sample-parallel march (rays in ray order, several lanes per
+ray, lane groups that read corner records piece by piece): views at the edges
+of its cuts against the FP64 oracle, a launch of more tiles than workgroups,
+tables beyond 32-bit offsets against the segment kernels, and corners whose
+neighbours in the table hold no number."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import oracle as O
+from paper_2112_05131_amd import binding as B
+from paper_2112_05131_amd.grid import Grid
+from tests.gpu_util import RGB_ATOL, make_pair, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _view(c2w, focal, w, h, scene=0, off=0):
+    v = B.PlxView()
+    v.c2w[:] = [float(x) for x in np.asarray(c2w, np.float64).reshape(12)]
+    v.focal, v.width, v.height, v.scene, v.reserved, v.out_offset = float(focal), w, h, scene, 0, off
+    return v
+
+
+def _render(grid, views, n):
+    out = torch.full((3 * n,), -1.0, device="cuda")
+    q = B.views_queue()
+    B.plx_render_views(B.SceneTable([grid]), views, out, q)
+    B.plx_render_views_status(q)
+    return out.view(n, 3)
+
+
+def _pose(seed, radius=2.0):
+    return synth.sphere_poses(1, seed=seed, radius=radius)[0].numpy()
+
+
+# 1 ray; a tile's edge and its neighbours; both sides of the rules at 2^16 and
+# 3 * 2^18 pixels (256x256 and 1024x768)
+SIZES = [(1, 1), (2, 3), (5, 7), (255, 257), (256, 256), (1024, 767), (1025, 768)]
+
+
+@pytest.mark.parametrize("sh_dtype", [B.PLX_F32, B.PLX_BF16, B.PLX_F16])
+@pytest.mark.parametrize("w,h", SIZES)
+def test_view_sizes_match_oracle(sh_dtype, w, h):
+    """Colours of (at most 3000 sampled) pixels; a random mask leaves NULL
+    corners in most cells.  Tolerance: the stated RGB bound."""
+    say("march", sh_dtype, w, h)
+    sv = synth.dense_random((23, 31, 18), seed=7, occupancy=0.35)
+    og, gg = make_pair(sv, sh_dtype=sh_dtype)
+    c2w, focal = _pose(11), 0.5 * w / math.tan(0.25)
+    got = _render(gg, [_view(c2w, focal, w, h)], w * h)
+    o, d = O.camera_rays(c2w, focal, w, h)
+    sel = np.sort(np.random.default_rng(5).choice(w * h, min(3000, w * h), replace=False))
+    ref = O.render_fwd(og, o[sel], d[sel])[0]
+    err = np.abs(got[torch.from_numpy(sel).cuda()].cpu().double().numpy() - ref).max()
+    assert err <= RGB_ATOL, err
+    assert torch.all(got >= 0)  # every pixel written
+
+
+def test_axis_parallel_rays_match_oracle():
+    """Rays along each axis (zero direction components) and through a grid
+    with long empty stretches, both ways."""
+    say("march: axis-parallel")
+    sv = synth.blob_scene((70, 40, 120), n_blobs=3, occupancy=0.01, seed=4)
+    og, gg = make_pair(sv)
+    for axis in range(3):
+        for sign in (1.0, -1.0):
+            # one pixel whose centre is the optical axis
+            fwd = np.zeros(3)
+            fwd[axis] = sign
+            up = np.eye(3)[(axis + 1) % 3]
+            right = np.cross(fwd, up)
+            blob = sv.mask.reshape(sv.reso).nonzero().double().mean(0).numpy()
+            c = (blob + 0.5) / np.array(sv.reso) - 0.5 - 2.0 * fwd
+            c2w = np.stack([right, up, -fwd, c], axis=1)
+            got = _render(gg, [_view(c2w, 10.0, 1, 1)], 1).cpu().double().numpy()
+            o, d = O.camera_rays(c2w, 10.0, 1, 1)
+            assert np.count_nonzero(d[0]) == 1
+            assert np.abs(got - O.render_fwd(og, o, d)[0]).max() <= RGB_ATOL
+
+
+def test_more_tiles_than_workgroups():
+    """4200x4200 pixels are 1.1M tiles of a launch of 2^20 workgroups: the
+    tiles beyond it equal those of the lower part rendered as a view alone
+    (the same rays: a view of twice the height around the same axis)."""
+    say("march: more tiles than workgroups")
+    sv = synth.blob_scene((40, 40, 40), n_blobs=5, occupancy=0.2, seed=8)
+    og, gg = make_pair(sv)
+    w, h = 4200, 4200
+    c2w, focal = _pose(3), 0.5 * w / math.tan(0.25)
+    got = _render(gg, [_view(c2w, focal, w, h)], w * h)
+    assert torch.all(got >= 0)
+    o, d = O.camera_rays(c2w, focal, w, h)
+    rng = np.random.default_rng(6)
+    sel = np.concatenate([rng.choice(w * h, 1500), w * h - 1 - rng.choice(4 * w, 1500)])
+    ref = O.render_fwd(og, o[sel], d[sel])[0]
+    assert np.abs(got[torch.from_numpy(sel).cuda()].cpu().double().numpy() - ref).max() <= RGB_ATOL
+
+
+@pytest.mark.parametrize("sh_dtype,reso", [(B.PLX_F32, (336, 320, 320)), (B.PLX_F16, (420, 416, 400))])
+def test_tables_beyond_32_bit_offsets(sh_dtype, reso):
+    """Dense grids whose records take more than 4 GiB (64-bit addresses)
+    against the segment kernels.  Two FP32 evaluations of the same samples:
+    twice the stated RGB bound at most."""
+    say("march: wide tables", sh_dtype)
+    n = reso[0] * reso[1] * reso[2]
+    assert n * B.plx_record_bytes(sh_dtype) > 1 << 32
+    rec = torch.zeros(n, 32, dtype=torch.float32, device="cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    for s in range(27):
+        rec[:, s] = torch.rand(n, generator=g, device="cuda") * 0.2 - 0.1 + (2.0 if s % 9 == 0 else 0.0)
+    rec[:, 28] = torch.rand(n, generator=g, device="cuda") * 20 - 5
+    index = torch.arange(n, dtype=torch.int32, device="cuda")
+    if sh_dtype != B.PLX_F32:
+        r16 = torch.empty(n, 32, dtype=torch.int16, device="cuda")
+        B.plx_records_convert(B.PLX_F32, rec, sh_dtype, r16, n)
+        rec = r16
+    grid = Grid(reso, index, rec, sh_dtype)
+    c2w, w, h = _pose(21), 120, 90
+    focal = 0.5 * w / math.tan(0.3)
+    got = _render(grid, [_view(c2w, focal, w, h)], w * h)
+    o, d = (torch.from_numpy(x).float().cuda() for x in O.camera_rays(c2w, focal, w, h))
+    ref = torch.empty(w * h, 3, device="cuda")
+    B.plx_render_fwd(grid.desc(), o.contiguous(), d.contiguous(), ref)
+    assert (got - ref).abs().max().item() <= 2 * RGB_ATOL
+    del rec, index, grid
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("sh_dtype", [B.PLX_F32, B.PLX_F16])
+def test_numbers_of_other_voxels_do_not_leak(sh_dtype):
+    """The first and last records of the table hold infinities and NaN: only
+    rays that read them may differ from the finite grid's render."""
+    say("march: non-finite records", sh_dtype)
+    sv = synth.dense_random((20, 20, 20), seed=9, occupancy=0.3)
+    _, gg = make_pair(sv, sh_dtype=sh_dtype)
+    c2w, w, h = _pose(2), 64, 48
+    focal = 0.5 * w / math.tan(0.45)  # the whole box, corners too
+    clean = _render(gg, [_view(c2w, focal, w, h)], w * h).clone()
+    o, d = O.camera_rays(c2w, focal, w, h)
+    og, _ = make_pair(sv, sh_dtype=sh_dtype)
+    bad = (0, sv.n_vox - 1)
+    for i in bad:  # every value of the record (the FP32 density included)
+        gg.data[i] = float("nan") if sh_dtype == B.PLX_F32 else -1
+    got = _render(gg, [_view(c2w, focal, w, h)], w * h)
+    # rays that read a bad voxel: their colour changes with its density
+    dens = sv.density.double().numpy().copy()
+    base = O.render_fwd(og, o, d)[1]
+    dens[list(bad)] += 1000.0
+    og2 = O.make_grid(np.array(sv.reso, np.int32), sv.mask.numpy(), dens, sv.sh.double().numpy())
+    reads = O.render_fwd(og2, o, d)[1] != base
+    keep = torch.from_numpy(~reads.reshape(-1)).cuda()
+    assert 0 < int((~keep).sum()) < w * h // 2
+    assert torch.equal(got[keep], clean[keep])
