@@ -439,7 +439,8 @@ int plx_bins_verify(const plx_grid *grid, const plx_bins *bins, plx_stream strea
  * is composited with Eq. (1) and the background is added with the remaining
  * transmittance.  Outputs (device float32): rgb_out[n_rays][3] and tau_out[n_rays]
  * = sum sigma_k delta_k (the optical depth, so T_final = exp(-tau)).  tau_out
- * may be NULL.  bins: the segment lists of these rays (plx_bins). */
+ * may be NULL.  bins: the segment lists of these rays (plx_bins); batches
+ * below 786,432 rays are marched in ray order, as by plx_render_fwd_rays. */
 int plx_render_fwd(const plx_grid *grid, const plx_render_opts *opts, const float *rays_o,
                    const float *rays_d, int64_t n_rays, const plx_bins *bins, float *rgb_out,
                    float *tau_out, plx_stream stream);
@@ -488,6 +489,39 @@ int plx_render_train_static(const plx_grid *grid, const plx_render_opts *opts, c
                             const float *rays_d, const float *target, int64_t n_rays,
                             float loss_scale, float *rgb_out, float *grad, uint8_t *touched,
                             double *loss_sum, plx_stream stream);
+
+/* The render calls in ray order, without segment lists: the same samples and
+ * terms (the order of FP32 additions may differ) for renders, and for gradient
+ * batches that put few rays into each brick (about the paper's 5000-ray
+ * batches).  Asynchronous; they allocate nothing.
+ *
+ * ray_ws and samp_ws: caller-owned device memory, 256-byte aligned, of
+ * plx_rays_ray_bytes(n_rays) and plx_rays_samp_bytes(n_rays, cap) bytes (0 for
+ * bad arguments), 1 <= cap <= 2^20.  A forward records each ray's optical
+ * depth (FP64), its number of occupied samples and up to `cap` of them (index
+ * and pre-activation values); a backward replays those, and finds and
+ * evaluates the samples beyond the cap again.
+ *
+ * plx_render_fwd_rays: plx_render_fwd; with ray_ws and samp_ws NULL nothing is
+ * recorded.  plx_render_bwd_rays: plx_render_bwd, from the workspaces as
+ * plx_render_fwd_rays left them for the same rays, grid and cap (it may be
+ * repeated).  plx_render_train_rays: plx_render_train; the workspaces are its
+ * scratch.  Calls that share workspaces must be ordered on a stream. */
+int64_t plx_rays_ray_bytes(int64_t n_rays);
+int64_t plx_rays_samp_bytes(int64_t n_rays, int32_t cap);
+int plx_render_fwd_rays(const plx_grid *grid, const plx_render_opts *opts, const float *rays_o,
+                        const float *rays_d, int64_t n_rays, float *rgb_out, float *tau_out, void *ray_ws,
+                        int64_t ray_ws_bytes, void *samp_ws, int64_t samp_ws_bytes, int32_t cap,
+                        plx_stream stream);
+int plx_render_bwd_rays(const plx_grid *grid, const plx_render_opts *opts, const float *rays_o,
+                        const float *rays_d, int64_t n_rays, const float *grad_rgb, void *ray_ws,
+                        int64_t ray_ws_bytes, void *samp_ws, int64_t samp_ws_bytes, int32_t cap,
+                        float *grad, uint8_t *touched, plx_stream stream);
+int plx_render_train_rays(const plx_grid *grid, const plx_render_opts *opts, const float *rays_o,
+                          const float *rays_d, const float *target, int64_t n_rays, void *ray_ws,
+                          int64_t ray_ws_bytes, void *samp_ws, int64_t samp_ws_bytes, int32_t cap,
+                          float loss_scale, float *rgb_out, float *grad, uint8_t *touched,
+                          double *loss_sum, plx_stream stream);
 
 /* Per-voxel maximum sample weight, the statistic of pruning by weight
  * (Sec. 3.4, the method of PlenOctrees).  Sample k of a ray has the weight

@@ -1,6 +1,7 @@
 """torch.autograd binding of the renderer: forward = plx_render_fwd, backward
-= plx_render_bwd (reverse replay with recomputed transmittance; only the rays,
-the per-ray optical depth and the batch's segment lists are saved)."""
+= plx_render_bwd (reverse replay with recomputed transmittance).  Saved are
+the rays, the per-ray optical depth and, for a batch in ray order, its occupied
+samples' values, else its segment lists."""
 from __future__ import annotations
 
 import torch
@@ -20,24 +21,34 @@ class RenderFn(torch.autograd.Function):
     def forward(ctx, params, grid, rays_o, rays_d, bg):
         n = rays_o.shape[0]
         rgb = torch.empty(n, 3, dtype=torch.float32, device=rays_o.device)
-        tau = torch.empty(n, dtype=torch.float32, device=rays_o.device)
         desc = grid.desc()
-        bins = B.make_bins(desc, rays_o, rays_d)
-        B.plx_render_fwd(desc, rays_o, rays_d, rgb, tau, bg, bins=bins)
-        ctx.save_for_backward(rays_o, rays_d, tau)
         ctx.grid = grid
-        ctx.bins = bins
         ctx.bg = tuple(bg)
+        if B.ray_order_grad(desc, n):
+            # in ray order, keeping the occupied samples' values
+            ctx.bins = None
+            work = B.make_ray_work(n, device=rays_o.device)
+            B.plx_render_fwd_rays(desc, rays_o, rays_d, rgb, None, work, bg)
+            ctx.save_for_backward(rays_o, rays_d, work.ray_ws, work.samp_ws)
+        else:
+            tau = torch.empty(n, dtype=torch.float32, device=rays_o.device)
+            ctx.bins = B.make_bins(desc, rays_o, rays_d)
+            B.plx_render_fwd(desc, rays_o, rays_d, rgb, tau, bg, bins=ctx.bins)
+            ctx.save_for_backward(rays_o, rays_d, tau)
         return rgb
 
     @staticmethod
     def backward(ctx, grad_rgb):
-        rays_o, rays_d, tau = ctx.saved_tensors
+        rays_o, rays_d, *saved = ctx.saved_tensors
         g = ctx.grid
         grad = torch.zeros(g.n_vox, B.REC_SLOTS, dtype=torch.float32, device=rays_o.device)
         touched = torch.zeros(g.n_vox, dtype=torch.uint8, device=rays_o.device)
-        B.plx_render_bwd(g.desc(), rays_o, rays_d, grad_rgb.contiguous().float(), tau, grad,
-                         touched, ctx.bg, bins=ctx.bins)
+        grad_rgb = grad_rgb.contiguous().float()
+        if ctx.bins is None:
+            work = B.RayWork(rays_o.shape[0], *saved, B.RAY_CAP)
+            B.plx_render_bwd_rays(g.desc(), rays_o, rays_d, grad_rgb, work, grad, touched, ctx.bg)
+        else:
+            B.plx_render_bwd(g.desc(), rays_o, rays_d, grad_rgb, saved[0], grad, touched, ctx.bg, bins=ctx.bins)
         return grad, None, None, None, None
 
 

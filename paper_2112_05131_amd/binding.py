@@ -146,6 +146,12 @@ _SIGS = {
     "plx_render_fwd": ([_GP, _OP, _P, _P, _I64, _BP, _P, _P, _P], ctypes.c_int),
     "plx_render_bwd": ([_GP, _OP, _P, _P, _I64, _BP, _P, _P, _P, _P, _P], ctypes.c_int),
     "plx_render_train": ([_GP, _OP, _P, _P, _P, _I64, _BP, _F, _P, _P, _P, _P, _P], ctypes.c_int),
+    "plx_render_fwd_rays": ([_GP, _OP, _P, _P, _I64, _P, _P, _P, _I64, _P, _I64, _I32, _P], ctypes.c_int),
+    "plx_render_bwd_rays": ([_GP, _OP, _P, _P, _I64, _P, _P, _I64, _P, _I64, _I32, _P, _P, _P], ctypes.c_int),
+    "plx_rays_ray_bytes": ([_I64], _I64),
+    "plx_rays_samp_bytes": ([_I64, _I32], _I64),
+    "plx_render_train_rays": ([_GP, _OP, _P, _P, _P, _I64, _P, _I64, _P, _I64, _I32, _F, _P, _P, _P, _P, _P],
+                              ctypes.c_int),
     "plx_render_max_weight": ([_GP, _P, _P, _I64, _BP, _P, _P], ctypes.c_int),
     "plx_render_train_static": ([_GP, _OP, _P, _P, _P, _I64, _F, _P, _P, _P, _P, _P], ctypes.c_int),
     "plx_render_state_bytes": ([_I64, _I32], _I64),
@@ -520,11 +526,72 @@ def _bins_for(g: PlxGrid, rays_o, rays_d, bins: Bins | None) -> Bins:
     return make_bins(g, rays_o, rays_d) if bins is None else bins
 
 
+# Occupied samples of a ray that the ray-order passes keep (20 bytes each); a
+# ray with more has the rest evaluated again.
+RAY_CAP = 512
+
+
+def ray_order(g: PlxGrid, n_rays: int) -> bool:
+    """Whether a fused training batch of n_rays rays is run in ray order
+    (plx_render_train_rays) rather than over segment lists.  In ray order
+    every ray sends a line of atomics per voxel it crosses, and nothing is
+    binned, counted or read back; the lists merge the rays of a brick.  The
+    batch's occupied brick crossings are estimated by n_rays times the bricks
+    along a ray times the share of occupied voxels.  Ray order / lists with
+    their binning (us, FP32): 5000 rays on 256^3 at 10% (16,000 crossings) 175 /
+    700, 5000 on a dense 64^3 (40,000) 164 / 590, 16,000 on 512^3 at 5% (51,000)
+    328 / 860; beyond the line it is only somewhat ahead or behind: 5000
+    inside a dense 128^3 (80,000) 599 / 960, 20,011 through a dense 256x256x128
+    (530,000) 1836 / 2180, 49,152 there 4129 / 3300."""
+    b = [-(-(int(r) - 1) // 8) for r in g.reso]
+    cells = int(g.reso[0]) * int(g.reso[1]) * int(g.reso[2])
+    return n_rays * sum(b) * int(g.n_vox) < 3 * 65536 * cells
+
+
+def ray_order_grad(g: PlxGrid, n_rays: int) -> bool:
+    """As ray_order, for a separate forward and backward pass, where lists
+    also cost a forward of their own: ray order while few rays cross a brick
+    (n_rays times the bricks along a ray over all bricks).  5000 rays on 64^3
+    (78) 164 / 277 us, 20,000 (312) 435 / 368; 65,536 on 256^3 (64) 530 / 1300
+    (FP16); 100,000 on 512^3 (24) 1143 / 1797; 16,384 inside a dense 128^3 (64)
+    1646 / 1440; 49,152 through a dense 256x256x128 (77) 4129 / 3302."""
+    b = [-(-(int(r) - 1) // 8) for r in g.reso]
+    return n_rays < 8192 or n_rays * sum(b) < 3 * 72 * b[0] * b[1] * b[2]
+
+
+class RayWork:
+    """Scratch of one gradient batch in ray order, taken by plx_render_train
+    in place of segment lists."""
+
+    def __init__(self, n_rays: int, ray_ws: torch.Tensor, samp_ws: torch.Tensor, cap: int):
+        self.n_rays, self.ray_ws, self.samp_ws, self.cap = n_rays, ray_ws, samp_ws, cap
+
+    def buffers(self):
+        return [self.ray_ws, self.samp_ws, None]
+
+
+def make_ray_work(n_rays: int, ray_ws: torch.Tensor | None = None, samp_ws: torch.Tensor | None = None,
+                  _unused=None, device=None, cap: int = RAY_CAP) -> RayWork:
+    """Scratch for n_rays rays, in the given buffers when they are large
+    enough, else in new ones."""
+    need = plx_rays_ray_bytes(n_rays), plx_rays_samp_bytes(n_rays, cap)
+    if ray_ws is None or ray_ws.numel() < need[0]:
+        ray_ws = workspace(need[0], device)
+    if samp_ws is None or samp_ws.numel() < need[1]:
+        samp_ws = workspace(need[1], device)
+    return RayWork(n_rays, ray_ws, samp_ws, cap)
+
+
 def plx_render_fwd(g: PlxGrid, rays_o, rays_d, rgb_out, tau_out=None, bg=(1.0, 1.0, 1.0),
                    bins: Bins | None = None, events=None):
+    """bins: the batch's segment lists where they exist already (without them
+    the rays are marched in ray order, which needs none)."""
     n = rays_o.shape[0]
     o = _opts(bg, None, n, None, events)
-    b = _bins_for(g, rays_o, rays_d, bins)
+    if bins is None:
+        plx_render_fwd_rays(g, rays_o, rays_d, rgb_out, tau_out, None, bg, events)
+        return
+    b = bins
     _check(lib().plx_render_fwd(ctypes.byref(g), ctypes.byref(o),
                                 _dptr(rays_o, "rays_o", torch.float32, 3 * n),
                                 _dptr(rays_d, "rays_d", torch.float32, 3 * n), n,
@@ -551,8 +618,16 @@ def plx_render_bwd(g: PlxGrid, rays_o, rays_d, grad_rgb, tau_fwd, grad, touched,
 
 def plx_render_train(g: PlxGrid, rays_o, rays_d, target, loss_scale, grad, touched, loss_sum,
                      rgb_out=None, bg=(1.0, 1.0, 1.0), priors: Priors | None = None, grad_bg=None,
-                     bins: Bins | None = None, events=None):
+                     bins: Bins | RayWork | None = None, events=None):
+    """bins: the batch's segment lists, or scratch for a batch in ray order;
+    made here (by ray_order) when not given."""
     n = rays_o.shape[0]
+    if bins is None and ray_order(g, n):
+        bins = make_ray_work(n, device=rays_o.device)
+    if isinstance(bins, RayWork):
+        plx_render_train_rays(g, rays_o, rays_d, target, loss_scale, grad, touched, loss_sum, bins, rgb_out, bg,
+                              priors, grad_bg, events)
+        return
     o = _opts(bg, priors, n, grad_bg, events)
     b = _bins_for(g, rays_o, rays_d, bins)
     _check(lib().plx_render_train(ctypes.byref(g), ctypes.byref(o),
@@ -581,6 +656,64 @@ def plx_render_train_static(g: PlxGrid, rays_o, rays_d, target, loss_scale, grad
                                          _dptr(grad, "grad", torch.float32, REC_SLOTS * g.n_vox),
                                          _dptr(touched, "touched", torch.uint8),
                                          _dptr(loss_sum, "loss_sum", torch.float64, 1), _stream()))
+
+
+def plx_rays_ray_bytes(n_rays: int) -> int:
+    return int(lib().plx_rays_ray_bytes(int(n_rays)))
+
+
+def plx_rays_samp_bytes(n_rays: int, cap: int) -> int:
+    return int(lib().plx_rays_samp_bytes(int(n_rays), int(cap)))
+
+
+def _work_args(work: RayWork | None, n: int):
+    if work is None:
+        return None, 0, None, 0, 0
+    if work.n_rays != n:
+        raise ValueError(f"scratch made for {work.n_rays} rays, the call has {n}")
+    return (_dptr(work.ray_ws, "ray_ws", torch.uint8), work.ray_ws.numel(), _dptr(work.samp_ws, "samp_ws", torch.uint8),
+            work.samp_ws.numel(), int(work.cap))
+
+
+def plx_render_fwd_rays(g: PlxGrid, rays_o, rays_d, rgb_out, tau_out=None, work: RayWork | None = None,
+                        bg=(1.0, 1.0, 1.0), events=None):
+    """plx_render_fwd in ray order; with work (make_ray_work) the occupied
+    samples are kept there for plx_render_bwd_rays."""
+    n = rays_o.shape[0]
+    o = _opts(bg, None, n, None, events)
+    _check(lib().plx_render_fwd_rays(ctypes.byref(g), ctypes.byref(o),
+                                     _dptr(rays_o, "rays_o", torch.float32, 3 * n),
+                                     _dptr(rays_d, "rays_d", torch.float32, 3 * n), n,
+                                     _dptr(rgb_out, "rgb_out", torch.float32, 3 * n),
+                                     _dptr(tau_out, "tau_out", torch.float32, n), *_work_args(work, n), _stream()))
+
+
+def plx_render_bwd_rays(g: PlxGrid, rays_o, rays_d, grad_rgb, work: RayWork, grad, touched, bg=(1.0, 1.0, 1.0),
+                        priors: Priors | None = None, grad_bg=None):
+    n = rays_o.shape[0]
+    o = _opts(bg, priors, n, grad_bg)
+    _check(lib().plx_render_bwd_rays(ctypes.byref(g), ctypes.byref(o),
+                                     _dptr(rays_o, "rays_o", torch.float32, 3 * n),
+                                     _dptr(rays_d, "rays_d", torch.float32, 3 * n), n,
+                                     _dptr(grad_rgb, "grad_rgb", torch.float32, 3 * n), *_work_args(work, n),
+                                     _dptr(grad, "grad", torch.float32, REC_SLOTS * g.n_vox),
+                                     _dptr(touched, "touched", torch.uint8), _stream()))
+
+
+def plx_render_train_rays(g: PlxGrid, rays_o, rays_d, target, loss_scale, grad, touched, loss_sum, work: RayWork,
+                          rgb_out=None, bg=(1.0, 1.0, 1.0), priors: Priors | None = None, grad_bg=None,
+                          events=None):
+    """plx_render_train in ray order, with work (make_ray_work) as scratch."""
+    n = rays_o.shape[0]
+    o = _opts(bg, priors, n, grad_bg, events)
+    _check(lib().plx_render_train_rays(ctypes.byref(g), ctypes.byref(o),
+                                       _dptr(rays_o, "rays_o", torch.float32, 3 * n),
+                                       _dptr(rays_d, "rays_d", torch.float32, 3 * n),
+                                       _dptr(target, "target", torch.float32, 3 * n), n, *_work_args(work, n),
+                                       float(loss_scale), _dptr(rgb_out, "rgb_out", torch.float32, 3 * n),
+                                       _dptr(grad, "grad", torch.float32, REC_SLOTS * g.n_vox),
+                                       _dptr(touched, "touched", torch.uint8),
+                                       _dptr(loss_sum, "loss_sum", torch.float64, 1), _stream()))
 
 
 def plx_render_state_bytes(n_rays: int, cap: int) -> int:

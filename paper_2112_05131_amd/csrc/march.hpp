@@ -2,6 +2,8 @@
 // sample-parallel march of rays in ray order.
 #pragma once
 
+#include <cmath>
+
 #include "plx_internal.hpp"
 
 namespace plx {
@@ -22,6 +24,49 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
 __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
+}
+
+// The optional sparsity (Cauchy) and beta priors of Sec. 3.7, as the gradient
+// kernels see them.
+struct Priors {
+    float lambda_s;    // Cauchy weight (0 = off)
+    float lambda_b;    // beta weight (0 = off)
+    float eps;         // beta epsilon
+    double *loss;      // [2] (L_s, L_b) ADDED, or NULL
+};
+
+// Beta prior of one ray from its optical depth tau (FP64; 1 - T = -expm1(-tau)
+// stays accurate for a nearly empty ray): returns dL_b/dsigma_k / delta_k =
+// -T dL_b/dT, the factor of each of its samples' density gradient, and adds
+// the ray's L_b to *loss.
+__device__ inline float beta_factor(const Priors &p, double tau, double *loss) {
+    const double T = exp(-tau), omT = -expm1(-tau), e = (double)p.eps;
+    *loss += (double)p.lambda_b * (log(e + T) + log(e + omT));
+    return (float)(-T * (double)p.lambda_b * (1.0 / (e + T) - 1.0 / (e + omT)));
+}
+
+// Cauchy prior at a sample with pre-activation density s > 0: the density
+// gradient lambda_s 4 s / (1 + 2 s^2); log(1 + 2 s^2) goes to *ls.
+__device__ __forceinline__ float cauchy_grad(const Priors &p, float s, float *ls) {
+    if (p.lambda_s == 0.0f || !(s > 0.0f)) return 0.0f;
+    *ls += log1pf(2.0f * s * s);
+    return 4.0f * (p.lambda_s * s) / (1.0f + 2.0f * s * s);
+}
+
+// Adds a wave's prior losses to p.loss (one atomic per wave and term; the
+// per-lane Cauchy sums are FP32, the wave sum FP64).
+__device__ inline void add_prior_loss(const Priors &p, float ls_lane, double lb) {
+    if (!p.loss) return;
+    double ls = (double)ls_lane;
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        ls += __shfl_xor(ls, m);
+        lb += __shfl_xor(lb, m);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        if (ls != 0.0) unsafeAtomicAdd(p.loss, (double)p.lambda_s * ls);
+        if (lb != 0.0) unsafeAtomicAdd(p.loss + 1, lb);
+    }
 }
 
 // Background colour of a ray: its own when the call gives one per ray.
@@ -321,11 +366,19 @@ template <int DT, int P, int M> struct Evaluator {
 // L / P, whose geometry r and sample count n all its P lanes hold (n = 0: no
 // ray).  march_basis must have filled the basis rows.  Returns, in every lane
 // of a ray, the colour before the background is added and the optical depth.
-// Called by the whole wave.
-template <int DT, int P, int M>
+// rec(i, k, v) gets the i-th occupied sample of a ray (sample index k, values
+// v) in the lane that composes it, when REC::kOn; the ray's number of occupied
+// samples goes to *count.  Called by the whole wave.
+struct NoRecord {
+    static constexpr bool kOn = false;
+    __device__ __forceinline__ void operator()(int, int, const float4 &) const {}
+};
+
+template <int DT, int P, int M, class REC>
 __device__ __forceinline__ void march_rays(const GridDev &g, MarchLds<P, M> &sh, const RayGeom &r, int n,
-                                           float C[3], double &tau) {
+                                           float C[3], double &tau, const REC &rec, int *count = nullptr) {
     static_assert(P * M <= 64 && (P & (P - 1)) == 0, "window");
+    int n_occ = 0;
     const int part = lane_id() % P, slot = lane_id() / P;
     C[0] = C[1] = C[2] = 0.0f;
     tau = 0.0;
@@ -402,12 +455,19 @@ __device__ __forceinline__ void march_rays(const GridDev &g, MarchLds<P, M> &sh,
         // compose the lane's samples, then the ray's lanes
         double tl = 0.0;
         float c[3] = {0.f, 0.f, 0.f};
+        int at = 0;  // the ray's number of the entry at `before`
+        if constexpr (REC::kOn) {
+            const int first = P == 64 ? 0 : __shfl(before, 0, P);
+            at = n_occ + before - first;
+            n_occ += (P == 64 ? total : __shfl(before + cnt, P - 1, P)) - first;
+        }
         {
             int e = before;
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 if ((mask >> i) & 1u) {
                     const float4 v = sh.pos[e];
+                    if constexpr (REC::kOn) rec(at + (e - before), kp + i, v);
                     ++e;
                     const float sd = fmaxf(v.x, 0.0f) * sample_at(g, r, kp + i).delta;
                     const float wk = expf(-(float)tl) * (-expm1f(-sd));
@@ -435,6 +495,36 @@ __device__ __forceinline__ void march_rays(const GridDev &g, MarchLds<P, M> &sh,
 #pragma unroll
         for (int a = 0; a < 3; ++a) C[a] += __shfl_xor(C[a], o, P);
     }
+    if constexpr (REC::kOn) *count = n_occ;
+}
+
+// ------------------------------------------------------------ host helpers
+
+inline int validate_rays(const float *o, const float *d, int64_t n, const char *fn) {
+    if (n < 0) return fail(PLX_EINVAL, "%s: n_rays < 0", fn);
+    if (n > ((int64_t)1 << 34)) return fail(PLX_EINVAL, "%s: n_rays too large", fn);
+    if (n > 0 && (!o || !d)) return fail(PLX_EINVAL, "%s: rays are NULL", fn);
+    return PLX_OK;
+}
+
+// Priors of a gradient call from its options (validated).
+inline int priors_from(const plx_render_opts *opts, Priors &p, const char *fn) {
+    p.lambda_s = opts->lambda_sparsity;
+    p.lambda_b = opts->lambda_beta;
+    p.eps = opts->beta_eps;
+    p.loss = opts->reg_loss_sum;
+    if (!std::isfinite(p.lambda_s) || !std::isfinite(p.lambda_b))
+        return fail(PLX_EINVAL, "%s: prior weights must be finite", fn);
+    if (p.lambda_b != 0.0f && !(p.eps > 0.0f && std::isfinite(p.eps)))
+        return fail(PLX_EINVAL, "%s: beta_eps must be > 0 when lambda_beta != 0", fn);
+    return PLX_OK;
+}
+
+// Records the caller's timing event i (when given) on the stream.
+inline int mark_event(void **events, int i, hipStream_t s, const char *fn) {
+    if (!events || !events[i]) return PLX_OK;
+    PLX_CHECK_HIP(hipEventRecord(static_cast<hipEvent_t>(events[i]), s), fn);
+    return PLX_OK;
 }
 
 }  // namespace plx

@@ -31,6 +31,10 @@ inline hipStream_t as_stream(plx_stream s) { return reinterpret_cast<hipStream_t
 int count_set_bits(const uint32_t *words, int64_t n_bits, void *ws, int64_t *count_out,
                    hipStream_t s, const char *fn);
 
+// Forward rendering in ray order (ray_order.hip); arguments validated.
+int render_fwd_rays(const plx_grid *grid, const plx_render_opts *opts, const float *rays_o, const float *rays_d,
+                    int64_t n_rays, float *rgb_out, float *tau_out, hipStream_t s, const char *fn);
+
 // Validates a grid descriptor for kernels; need_occ for the render calls.
 int validate_grid(const plx_grid *g, bool need_occ, const char *fn);
 

@@ -111,11 +111,12 @@ class RaySampler:
         return o, d, t
 
 
-# Batches from this size on use the recorded backward (sample buffer and one
-# scatter workgroup per brick).  Smaller batches put few segments in each
-# brick, so the per-brick set-up of the scatter outweighs what it saves on
-# atomics, and the replay's own scatter is faster: at 5000-ray batches on a
-# 256^3 grid a step takes 0.62 ms with it and 0.79 ms with the recorded one.
+# Batches over segment lists use the recorded backward (sample buffer and one
+# scatter workgroup per brick) from this size on.  Smaller batches put few
+# segments in each brick, so the per-brick set-up of the scatter outweighs what
+# it saves on atomics, and the replay's own scatter is faster: 49,152 rays on
+# 512^3 take 0.64 ms with it and 1.06 ms with the recorded one, 20,011 through a
+# dense 256x256x128 grid 1.97 and 2.25.
 RECORDED_MIN_RAYS = 1 << 16
 
 
@@ -125,10 +126,11 @@ def recorded_backward(n_rays: int) -> bool:
 
 class StepEvents:
     """Device events around the calls of one training step (timing only):
-    the binning of its batch (on the stream that made the bins), the four
-    events the fused render call records between its kernels (before the
-    segment forward, after it, after the per-ray combine, after the segment
-    backward), and the ends of TV and of RMSProp."""
+    the preparation of its batch (gather and binning, on the stream that
+    made it), the four events the fused render call records between its
+    kernels (before the forward, after it, after the per-ray combine, which a
+    batch in ray order does not have, after the backward), and the ends of TV
+    and of RMSProp."""
 
     def __init__(self):
         ev = lambda: torch.cuda.Event(enable_timing=True)  # noqa: E731
@@ -158,8 +160,8 @@ class Trainer:
         self.cfg = cfg or TrainConfig()
         self.rng = np.random.default_rng(seed)
         self.step_id = 0
-        # the two alternating sets of segment-list buffers of run() and the
-        # completion events of the steps that last used them, kept across
+        # the two alternating sets of segment-list (or scratch) buffers of
+        # run() and the completion events of the steps that last used them, kept across
         # calls so that a new call neither allocates them again nor refills
         # a set that a step of the previous call may still be reading
         self._run_bufs = [[None, None, None], [None, None, None]]
@@ -223,13 +225,14 @@ class Trainer:
     def step(self, rays_o, rays_d, target, tv: bool = True, rgb_out=None, bins=None,
              events: StepEvents | None = None):
         """One optimisation step on a ray batch (all device tensors).  bins:
-        the batch's segment lists (binding.make_bins), made here when not
-        given; events: recorded around the step's calls when given."""
+        the batch's segment lists (binding.make_bins) or scratch in ray order
+        (binding.make_ray_work), made here when not given;
+        events: recorded around the step's calls when given."""
         c, g = self.cfg, self.grid
         lr_s, lr_h = self.learning_rates()
         n = rays_o.shape[0]
         rev = events.render if events is not None else None
-        if bins is None:
+        if bins is None and not B.ray_order(g.desc(), n):
             bins = B.make_bins(g.desc(), rays_o, rays_d, samples=recorded_backward(n))
         if self.bg is None:
             B.plx_render_train(g.desc(), rays_o, rays_d, target, 1.0 / max(n, 1), self.grad,
@@ -272,8 +275,9 @@ class Trainer:
             events: list | None = None):
         """n_steps optimisation steps on consecutive batches of the sampler.
 
-        With overlap, batch t+1 is gathered and binned on a second stream
-        while step t runs on the current one: the binning reads only the rays
+        With overlap, batch t+1 is gathered and (where it is not rendered in
+        ray order) binned on a second stream while step t runs on the current
+        one: the binning reads only the rays
         and the grid's occupancy, which a step does not change, and its one
         synchronising call (the segment count) then waits for that stream
         alone, so the device never idles on it.  The two sets of batch and
@@ -303,7 +307,11 @@ class Trainer:
                 if bb is None or bb[0].shape[0] != sampler.batch or bb[0].device != sampler.o.device:
                     bb = self._run_batch[slot] = sampler.batch_buffers()
                 o, d, t = sampler.next_batch(out=bb)
-                b = B.make_bins(self.grid.desc(), o, d, *bufs[slot], samples=recorded_backward(o.shape[0]))
+                desc = self.grid.desc()
+                if B.ray_order(desc, o.shape[0]):
+                    b = B.make_ray_work(o.shape[0], *bufs[slot], device=o.device)
+                else:
+                    b = B.make_bins(desc, o, d, *bufs[slot], samples=recorded_backward(o.shape[0]))
                 bufs[slot] = b.buffers()
                 if se is not None:
                     se.bins[1].record(side)

@@ -13,7 +13,8 @@ import synth
 from oracle import oracle as O
 from paper_2112_05131_amd import binding as B
 from paper_2112_05131_amd.grid import Grid
-from tests.gpu_util import RGB_ATOL, make_pair, say
+from tests.gpu_util import RGB_ATOL, assert_grads_close, assert_touched_equal, grad_mass, make_pair, say
+from tests.test_gpu_priors import prior_mass
 
 pytestmark = pytest.mark.gpu
 
@@ -156,3 +157,112 @@ def test_numbers_of_other_voxels_do_not_leak(sh_dtype):
     keep = torch.from_numpy(~reads.reshape(-1)).cuda()
     assert 0 < int((~keep).sum()) < w * h // 2
     assert torch.equal(got[keep], clean[keep])
+
+
+# one ray; a few with room for one sample each; records that end inside, at and
+# past windows of 64; both forward mappings (from 16,384 rays on); long runs of
+# samples in one cell (steps of 0.1 voxel) and rays that miss
+RAY_CASES = [(B.PLX_F32, 1, 512, 0.5), (B.PLX_F32, 65, 1, 0.5), (B.PLX_F32, 1500, 64, 0.1), (B.PLX_BF16, 1500, 63, 0.1),
+             (B.PLX_F16, 1500, 130, 0.5), (B.PLX_F32, 16389, 512, 0.5), (B.PLX_F16, 16389, 20, 0.5)]
+
+
+@pytest.mark.parametrize("sh_dtype,n,cap,step", RAY_CASES)
+@pytest.mark.parametrize("priors", [False, True])
+def test_ray_order_gradients_match_oracle(sh_dtype, n, cap, step, priors):
+    """The fused training call in ray order, and forward + backward through
+    the same workspaces (the backward twice: it leaves the record as it is),
+    against the oracle, with per-ray backgrounds; touched sets bit for bit.
+    Tolerances: the stated ones of gradients, losses and colours."""
+    say("ray order", sh_dtype, n, cap, step, priors)
+    sv = synth.dense_random((27, 22, 30), seed=81, occupancy=0.45, sigma_lo=-5.0, sigma_hi=20.0, ho_scale=0.3)
+    og, gg = make_pair(sv, sh_dtype, step_voxels=step)
+    o, d = synth.random_rays(n, seed=82)
+    o[3::7] += 5.0  # misses
+    on, dn = o.numpy(), d.numpy()
+    rng = np.random.default_rng(83)
+    tgt = rng.uniform(0.0, 1.0, (n, 3)).astype(np.float32)
+    bgr = rng.uniform(0.0, 1.0, (n, 3)).astype(np.float32)
+    oc, dc, bgc = o.cuda(), d.cuda(), torch.from_numpy(bgr).cuda()
+    ls, lb, eps = (1e-3, 1e-2, 1e-3) if priors else (0.0, 0.0, 1e-3)
+    m = gg.n_vox
+    desc = gg.desc()
+    work = B.make_ray_work(n, cap=cap)
+    grad = torch.zeros(m, 32, device="cuda")
+    touched = torch.zeros(m, dtype=torch.uint8, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    pl = torch.zeros(2, dtype=torch.float64, device="cuda")
+    rgb, gbg = torch.empty(n, 3, device="cuda"), torch.empty(n, 3, device="cuda")
+    pri = B.Priors(ls, lb, eps, pl) if priors else None
+    B.plx_render_train(desc, oc, dc, torch.from_numpy(tgt).cuda(), 1.0 / n, grad, touched, loss, rgb, bgc, pri, gbg,
+                       bins=work)
+    rgb_ref, t_fin = O.render_fwd(og, on, dn, bgr)[0], np.exp(-O.render_fwd(og, on, dn, bgr)[1])
+    assert np.abs(rgb.cpu().double().numpy() - rgb_ref).max() <= RGB_ATOL
+    g_rgb, loss_ref = O.mse_grad(rgb_ref, tgt)
+    assert abs(loss.item() - loss_ref) <= 1e-5 * loss_ref
+    # T_final (C - target) 2/R: both factors within the colour bound
+    assert np.abs(gbg.cpu().double().numpy() - t_fin[:, None] * g_rgb).max() <= 4 * RGB_ATOL / n
+    gd, gs, t_ref = O.render_bwd(og, on, dn, g_rgb, bgr)
+    md, ms = grad_mass(og, on, dn, g_rgb, bgr, chain_rays=n)
+    if priors:
+        ls_ref, lb_ref, gd_p, _ = O.regularisers(og, on, dn, ls, lb, eps)
+        got = pl.cpu().numpy()
+        assert abs(got[0] - ls_ref) <= 1e-4 * abs(ls_ref) + 1e-12
+        assert abs(got[1] - lb_ref) <= 1e-6 * abs(lb_ref) + 1e-9
+        gd, md = gd + gd_p, md + prior_mass(og, on, dn, ls, lb, eps)
+    assert_touched_equal(touched, t_ref, "ray order train")
+    assert_grads_close(grad, gd, gs, "ray order train", (md, ms))
+
+    # separate calls on the same workspaces
+    G = rng.normal(size=(n, 3)) * 1e-3
+    Gc = torch.from_numpy(G).float().cuda()
+    rgb2, tau = torch.empty(n, 3, device="cuda"), torch.empty(n, device="cuda")
+    B.plx_render_fwd_rays(desc, oc, dc, rgb2, tau, work, bgc)
+    assert torch.equal(rgb2, rgb)
+    plain = torch.empty(n, 3, device="cuda")
+    B.plx_render_fwd_rays(desc, oc, dc, plain, None, None, bgc)
+    assert torch.equal(plain, rgb)
+    Gd = Gc.cpu().double().numpy()
+    gd, gs, _ = O.render_bwd(og, on, dn, Gd, bgr)
+    md, ms = grad_mass(og, on, dn, Gd, bgr)
+    if priors:
+        gd, md = gd + gd_p, md + prior_mass(og, on, dn, ls, lb, eps)
+    for _ in range(2):
+        grad.zero_()
+        touched.zero_()
+        B.plx_render_bwd_rays(desc, oc, dc, Gc, work, grad, touched, bgc, pri, gbg)
+        assert_touched_equal(touched, t_ref, "ray order bwd")
+        assert_grads_close(grad, gd, gs, "ray order bwd", (md, ms))
+        assert np.abs(gbg.cpu().double().numpy() - t_fin[:, None] * Gd).max() <= 1e-5 * np.abs(Gd).max()
+
+
+@pytest.mark.parametrize("n", [3000, 60000])
+def test_autograd_both_routes(n):
+    """render() in a loss, below and above the rule for ray order, against
+    the oracle; a second backward of a retained graph adds the same again."""
+    from paper_2112_05131_amd.autograd import render
+    say("autograd routes", n)
+    og, gg = make_pair(synth.dense_random((20, 24, 22), seed=31, occupancy=0.5, ho_scale=0.2))
+    assert B.ray_order_grad(gg.desc(), n) == (n == 3000)
+    o, d = synth.random_rays(n, seed=32)
+    G = torch.from_numpy(np.random.default_rng(33).normal(size=(n, 3))).float()
+    params = gg.param_records().requires_grad_()
+    rgb = render(gg, o.cuda(), d.cuda())
+    loss = (rgb * G.cuda()).sum()
+    loss.backward(retain_graph=True)
+    first = params.grad.clone()
+    loss.backward()
+    gd, gs, _ = O.render_bwd(og, o.numpy(), d.numpy(), G.double().numpy())
+    mass = grad_mass(og, o.numpy(), d.numpy(), G.double().numpy())
+    assert_grads_close(first, gd, gs, "autograd", mass)
+    assert_grads_close(params.grad, 2 * gd, 2 * gs, "autograd twice", (2 * mass[0], 2 * mass[1]))
+
+
+def test_ray_work_of_another_batch_is_refused():
+    _, gg = make_pair(synth.dense_random((9, 9, 9), seed=1))
+    o, d = synth.random_rays(40, seed=2)
+    rgb = torch.empty(40, 3, device="cuda")
+    with pytest.raises(ValueError, match="made for"):
+        B.plx_render_fwd_rays(gg.desc(), o.cuda(), d.cuda(), rgb, None, B.make_ray_work(39))
+    small = B.RayWork(40, B.workspace(256), B.workspace(256), 64)
+    with pytest.raises(B.PlxError, match="workspace"):
+        B.plx_render_fwd_rays(gg.desc(), o.cuda(), d.cuda(), rgb, None, small)
