@@ -730,7 +730,7 @@ def _state_ptr(state, n, cap):
 
 def plx_render_max_weight(g: PlxGrid, rays_o, rays_d, wmax, bins: Bins | None = None):
     n = rays_o.shape[0]
-    b = _bins_for(g, rays_o, rays_d, bins)
+    b = make_bins(g, rays_o, rays_d, samples=False) if bins is None else bins
     _check(lib().plx_render_max_weight(ctypes.byref(g),
                                        _dptr(rays_o, "rays_o", torch.float32, 3 * n),
                                        _dptr(rays_d, "rays_d", torch.float32, 3 * n), n,
