@@ -4,19 +4,26 @@
 // Size-changing operations are stream compactions over the cells in storage
 // order: a three-phase scan (per-block flag counts, one-block scan of the
 // counts, per-block local scan and write).  Table ids therefore follow
-// increasing storage id, as the index-grid definition requires.
+// increasing storage id, as the index-grid definition requires.  A block
+// of the last phase also makes the records of its occupied cells, 8 lanes (16
+// bytes each) per record: its table ids are consecutive, so the stores are
+// too.  Memory bounds these passes; a thread per cell that copied or
+// interpolated a whole record by itself took 545 us (copy) and 1413 us (index
+// and trilinear values) for 256x256x128 cells refined to 512x512x128, now
+// 146 and 473.
 #include "plx_internal.hpp"
 
 namespace plx {
 namespace {
 
 constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
+constexpr int kScanItems = 16;  // cells per thread
 constexpr int kScanTile = kScanThreads * kScanItems;
 
-// Exclusive scan of one int per thread over a 256-thread block.
+// Exclusive scan of one int per thread over a block of THREADS.
+template <int THREADS = kScanThreads>
 __device__ inline int block_exclusive_scan(int x, int *total) {
-    __shared__ int wsum[kScanThreads / 64];
+    __shared__ int wsum[THREADS / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int inc = x;
 #pragma unroll
@@ -28,7 +35,7 @@ __device__ inline int block_exclusive_scan(int x, int *total) {
     __syncthreads();
     int off = 0, tot = 0;
 #pragma unroll
-    for (int i = 0; i < kScanThreads / 64; ++i) {
+    for (int i = 0; i < THREADS / 64; ++i) {
         off += (i < w) ? wsum[i] : 0;
         tot += wsum[i];
     }
@@ -37,95 +44,192 @@ __device__ inline int block_exclusive_scan(int x, int *total) {
     return off + inc - x;
 }
 
-// ---- predicates over cells
+// ---- predicates over cells: flags<ITEMS>(v, n), the flags of the ITEMS cells
+// from v on (bit i: cell v + i; cells from n on are 0)
 struct MaskPred {
     const uint8_t *mask;
-    __device__ bool operator()(int64_t v) const { return mask[v] != 0; }
+    bool aligned;  // mask is 16-byte aligned
+    template <int ITEMS>
+    __device__ uint32_t flags(int64_t v, int64_t n) const {
+        uint32_t f = 0;
+        if (ITEMS == 16 && aligned && v + ITEMS <= n) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(mask + v);
+            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+            for (int i = 0; i < 16; ++i) f |= ((w[i >> 2] >> (8 * (i & 3)) & 0xffu) != 0u ? 1u : 0u) << i;
+        } else {
+            for (int i = 0; i < ITEMS; ++i)
+                if (v + i < n && mask[v + i] != 0) f |= 1u << i;
+        }
+        return f;
+    }
 };
 
-struct ParentPred {  // new cell occupied iff its parent cell is occupied
+// New cell occupied iff its parent cell is occupied: along each axis the
+// parent of cell k of nn is floor((2k + 1) on / (2 nn)).  Along the last axis
+// quotient and remainder go from cell to cell by additions; a division per
+// cell and axis took 115 us per pass over 33.6M cells, so 38 to 54.
+struct ParentPred {
     const int32_t *old_index;
     int on[3], nn[3];
-    __device__ bool operator()(int64_t v) const {
-        int k = (int)(v % nn[2]);
-        int64_t r = v / nn[2];
-        int j = (int)(r % nn[1]);
-        int i = (int)(r / nn[1]);
-        int pi = (int)(((int64_t)(2 * i + 1) * on[0]) / (2 * (int64_t)nn[0]));
-        int pj = (int)(((int64_t)(2 * j + 1) * on[1]) / (2 * (int64_t)nn[1]));
-        int pk = (int)(((int64_t)(2 * k + 1) * on[2]) / (2 * (int64_t)nn[2]));
-        return old_index[((int64_t)pi * on[1] + pj) * on[2] + pk] >= 0;
+    bool narrow;  // every product, and every cell, fits 32 bits
+    __device__ uint32_t quotient(uint64_t a, uint64_t b) const {
+        return narrow ? (uint32_t)a / (uint32_t)b : (uint32_t)(a / b);
+    }
+    __device__ void decode(int64_t v, int &i, int &j, int &k) const {
+        if (narrow) {
+            const uint32_t r = (uint32_t)v / (uint32_t)nn[2];
+            k = (int)((uint32_t)v - r * nn[2]);
+            i = (int)(r / (uint32_t)nn[1]);
+            j = (int)(r - (uint32_t)i * nn[1]);
+        } else {
+            const int64_t r = v / nn[2];
+            k = (int)(v - r * nn[2]);
+            i = (int)(r / nn[1]);
+            j = (int)(r - (int64_t)i * nn[1]);
+        }
+    }
+    __device__ const int32_t *row(int i, int j) const {
+        const int pi = (int)quotient((uint64_t)(2 * (int64_t)i + 1) * on[0], 2 * (uint64_t)nn[0]);
+        const int pj = (int)quotient((uint64_t)(2 * (int64_t)j + 1) * on[1], 2 * (uint64_t)nn[1]);
+        return old_index + ((int64_t)pi * on[1] + pj) * on[2];
+    }
+    template <int ITEMS>
+    __device__ uint32_t flags(int64_t v, int64_t n) const {
+        if (v >= n) return 0u;
+        int i, j, k;
+        decode(v, i, j, k);
+        const int32_t *p = row(i, j);
+        const uint64_t den = 2 * (uint64_t)nn[2], num = (uint64_t)(2 * (int64_t)k + 1) * on[2];
+        const uint32_t q0 = quotient((uint64_t)on[2], den), dq = quotient(2 * (uint64_t)on[2], den);
+        const uint64_t r0 = on[2] - q0 * den, dr = 2 * (uint64_t)on[2] - dq * den;
+        uint32_t q = quotient(num, den);
+        uint64_t rem = num - q * den;
+        int32_t id[ITEMS];
+#pragma unroll
+        for (int e = 0; e < ITEMS; ++e) {
+            id[e] = v + e < n ? p[q] : -1;
+            q += dq;
+            rem += dr;
+            if (rem >= den) {
+                rem -= den;
+                ++q;
+            }
+            if (++k == nn[2]) {
+                k = 0;
+                q = q0;
+                rem = r0;
+                if (++j == nn[1]) {
+                    j = 0;
+                    ++i;
+                }
+                if (v + e + 1 < n) p = row(i, j);
+            }
+        }
+        uint32_t f = 0;
+#pragma unroll
+        for (int e = 0; e < ITEMS; ++e) f |= (id[e] >= 0 ? 1u : 0u) << e;
+        return f;
     }
 };
 
-template <class Pred>
-__global__ __launch_bounds__(kScanThreads) void scan_count_kernel(Pred pred, int64_t n,
+// Flag counts of the tiles of kScanThreads * ITEMS cells, 16 cells a thread
+// whatever ITEMS is (ITEMS <= 4: several tiles a workgroup).
+template <int ITEMS, class Pred>
+__global__ __launch_bounds__(kScanThreads) void scan_count_kernel(Pred pred, int64_t n, int64_t nb,
                                                                   int *counts) {
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    int c = 0;
+    constexpr int kWidth = kScanThreads * ITEMS / kScanItems;  // threads of a tile
+    static_assert(kWidth <= 64 || kWidth == kScanThreads, "a tile is a wave's lanes or a workgroup");
+    const int64_t t = (int64_t)blockIdx.x * kScanThreads + threadIdx.x;
+    int c = __popc(pred.template flags<kScanItems>(t * kScanItems, n));
+    if (kWidth == kScanThreads) {
+        int tot;
+        block_exclusive_scan(c, &tot);
+        c = tot;
+    } else {
 #pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-        int64_t v = base + i;
-        if (v < n && pred(v)) ++c;
+        for (int m = kWidth / 2; m >= 1; m >>= 1) c += __shfl_xor(c, m);
     }
-    int tot;
-    block_exclusive_scan(c, &tot);
-    if (threadIdx.x == 0) counts[blockIdx.x] = tot;
+    if (threadIdx.x % kWidth == 0 && t / kWidth < nb) counts[t / kWidth] = c;
 }
 
 // One block: exclusive scan of nb block counts into offsets[0..nb], offsets[nb]
-// = total.
-__global__ __launch_bounds__(kScanThreads) void scan_offsets_kernel(const int *counts, int64_t nb,
-                                                                    int64_t *offsets) {
-    __shared__ int64_t carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int64_t b0 = 0; b0 < nb; b0 += kScanThreads) {
-        int64_t b = b0 + threadIdx.x;
-        int c = b < nb ? counts[b] : 0;
-        int tot;
-        int ex = block_exclusive_scan(c, &tot);
-        int64_t base = carry;
-        if (b < nb) offsets[b] = base + ex;
+// = total.  8 counts a thread, moved in and out through LDS so that the
+// accesses are whole lines (one compute unit does them all: 62 us for 65,536
+// counts with 16 consecutive ones read by each thread, now 36).
+constexpr int kOffsetThreads = 1024, kOffsetItems = 8, kOffsetTile = kOffsetThreads * kOffsetItems;
+
+__global__ __launch_bounds__(kOffsetThreads) void scan_offsets_kernel(const int *counts, int64_t nb,
+                                                                      int64_t *offsets) {
+    __shared__ int sh[kOffsetTile + kOffsetThreads];  // count i at i + i / kOffsetItems
+    int64_t carry = 0;
+    for (int64_t b0 = 0; b0 < nb; b0 += kOffsetTile) {
+#pragma unroll
+        for (int u = 0; u < kOffsetItems; ++u) {
+            const int i = u * kOffsetThreads + threadIdx.x;
+            sh[i + i / kOffsetItems] = b0 + i < nb ? counts[b0 + i] : 0;
+        }
         __syncthreads();
-        if (threadIdx.x == 0) carry = base + tot;
+        int *mine = sh + threadIdx.x * (kOffsetItems + 1);
+        int sum = 0, tot;
+#pragma unroll
+        for (int u = 0; u < kOffsetItems; ++u) {
+            const int c = mine[u];
+            mine[u] = sum;
+            sum += c;
+        }
+        const int before = block_exclusive_scan<kOffsetThreads>(sum, &tot);
+#pragma unroll
+        for (int u = 0; u < kOffsetItems; ++u) mine[u] += before;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kOffsetItems; ++u) {
+            const int i = u * kOffsetThreads + threadIdx.x;
+            if (b0 + i < nb) offsets[b0 + i] = carry + sh[i + i / kOffsetItems];
+        }
+        carry += tot;
         __syncthreads();
     }
     if (threadIdx.x == 0) offsets[nb] = carry;
 }
 
-template <class Pred, class Writer>
+// Index entries of the tile's cells, and its records through wr: wr.item(v, e)
+// (what the list keeps of occupied cell v, the e-th of the tile) and
+// wr.records(list, n, first): the n records with ids from `first` on.
+template <int ITEMS, class Pred, class Writer>
 __global__ __launch_bounds__(kScanThreads) void scan_write_kernel(Pred pred, Writer wr, int64_t n,
+                                                                  int32_t *index_out,
                                                                   const int64_t *offsets) {
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    uint32_t flags = 0;
-    int c = 0;
-#pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-        int64_t v = base + i;
-        if (v < n && pred(v)) {
-            flags |= 1u << i;
-            ++c;
-        }
-    }
+    constexpr int kTile = kScanThreads * ITEMS;
+    __shared__ uint32_t flags_sh[kScanThreads];
+    __shared__ int rank_sh[kScanThreads];
+    __shared__ typename Writer::Item list[kTile];
+    const int64_t base = (int64_t)blockIdx.x * kTile;
+    const uint32_t flags = pred.template flags<ITEMS>(base + threadIdx.x * ITEMS, n);
     int tot;
-    int64_t rank = offsets[blockIdx.x] + block_exclusive_scan(c, &tot);
-#pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
-        int64_t v = base + i;
-        if (v >= n) break;
-        if (flags & (1u << i)) {
-            wr.occupied(v, rank);
-            ++rank;
-        } else {
-            wr.empty(v);
-        }
+    rank_sh[threadIdx.x] = block_exclusive_scan(__popc(flags), &tot);
+    flags_sh[threadIdx.x] = flags;
+    __syncthreads();
+    const int64_t first = offsets[blockIdx.x];
+#pragma unroll 4
+    for (int e = threadIdx.x; e < kTile; e += kScanThreads) {
+        if (base + e >= n) break;
+        const uint32_t f = flags_sh[e / ITEMS];
+        const int i = e % ITEMS;
+        const int local = rank_sh[e / ITEMS] + __popc(f & ((1u << i) - 1u));
+        const bool on = f >> i & 1u;
+        index_out[base + e] = on ? (int32_t)(first + local) : -1;
+        if (Writer::kRecords && on) list[local] = wr.item(base + e, e);
     }
+    if (!Writer::kRecords) return;
+    __syncthreads();
+    wr.records(list, tot, first);
 }
 
 // Workspace of the grid calls (caller-owned, plx_grid_workspace_bytes): a
-// 256-byte block of counters, then one byte per cell (the prune occupancy
-// flags), then the per-block counts and offsets of the compaction scan.
+// 256-byte block of counters, then one byte per cell (two bits are used, the
+// occupied and the stored cells of the prune), then the per-block counts and
+// offsets of the compaction scan.
 struct WsLayout {
     int64_t counters, bytes8, scan, bytes;
 };
@@ -161,42 +265,151 @@ int zero_counters(void *ws, hipStream_t s, const char *fn) {
     return check_launch(fn);
 }
 
-template <class Pred, class Writer>
-int run_scan(Pred pred, Writer wr, int64_t n, void *ws, hipStream_t s, const char *what) {
+// The counts and offsets lie where the prune keeps its bits: a compaction
+// needs one or the other.
+template <int ITEMS = kScanItems, class Pred, class Writer>
+int run_scan(Pred pred, Writer wr, int64_t n, int32_t *index_out, void *ws, hipStream_t s, const char *what) {
     if (n <= 0) return PLX_OK;
-    int64_t nb = scan_blocks(n);
-    if (nb > 0x7fffffff) return fail(PLX_EINVAL, "%s: too many cells", what);
-    const WsLayout l = ws_layout(n);
-    int64_t *offsets = reinterpret_cast<int64_t *>(static_cast<char *>(ws) + l.scan);
-    int *counts = reinterpret_cast<int *>(static_cast<char *>(ws) + l.scan + up256((nb + 1) * 8));
+    constexpr int64_t tile = kScanThreads * ITEMS;
+    const int64_t nb = (n + tile - 1) / tile;
+    if (scan_blocks(n) > 0x7fffffff / (kScanItems / ITEMS)) return fail(PLX_EINVAL, "%s: too many cells", what);
+    char *scan = static_cast<char *>(ws) + ws_layout(n).bytes8;
+    int64_t *offsets = reinterpret_cast<int64_t *>(scan);
+    int *counts = reinterpret_cast<int *>(scan + up256((nb + 1) * 8));
     int rc;
-    scan_count_kernel<<<(unsigned)nb, kScanThreads, 0, s>>>(pred, n, counts);
+    scan_count_kernel<ITEMS><<<(unsigned)scan_blocks(n), kScanThreads, 0, s>>>(pred, n, nb, counts);
     if ((rc = check_launch(what))) return rc;
-    scan_offsets_kernel<<<1, kScanThreads, 0, s>>>(counts, nb, offsets);
+    scan_offsets_kernel<<<1, kOffsetThreads, 0, s>>>(counts, nb, offsets);
     if ((rc = check_launch(what))) return rc;
-    scan_write_kernel<<<(unsigned)nb, kScanThreads, 0, s>>>(pred, wr, n, offsets);
+    scan_write_kernel<ITEMS><<<(unsigned)nb, kScanThreads, 0, s>>>(pred, wr, n, index_out, offsets);
     return check_launch(what);
 }
 
 // ---- writers
 struct IndexWriter {
-    int32_t *out;
-    __device__ void occupied(int64_t v, int64_t rank) const { out[v] = (int32_t)rank; }
-    __device__ void empty(int64_t v) const { out[v] = -1; }
+    static constexpr bool kRecords = false;
+    using Item = uint8_t;
+    __device__ uint8_t item(int64_t, int) const { return 0; }
+    __device__ void records(const uint8_t *, int, int64_t) const {}
 };
 
+// CHUNKS: 16-byte chunks per record, one lane each.
+template <int CHUNKS>
 struct PruneWriter {
-    int32_t *out;
+    static constexpr bool kRecords = true;
+    using Item = int32_t;
     const int32_t *old_index;
-    const uint4 *old_data;  // records as 16-byte chunks
+    const uint4 *old_data;
     uint4 *new_data;
-    int chunks;             // 16-byte chunks per record
-    __device__ void occupied(int64_t v, int64_t rank) const {
-        out[v] = (int32_t)rank;
-        int64_t src = (int64_t)old_index[v] * chunks, dst = rank * chunks;
-        for (int c = 0; c < chunks; ++c) new_data[dst + c] = old_data[src + c];
+    __device__ int32_t item(int64_t v, int) const { return old_index[v]; }
+    __device__ void records(const int32_t *list, int n, int64_t first) const {
+        const int L = threadIdx.x % CHUNKS;
+        constexpr int step = kScanThreads / CHUNKS;
+        int e = threadIdx.x / CHUNKS;
+        // four records in flight per lane
+        for (; e + 3 * step < n; e += 4 * step) {
+            uint4 x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = old_data[(int64_t)list[e + u * step] * CHUNKS + L];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) new_data[(first + e + u * step) * CHUNKS + L] = x[u];
+        }
+        for (; e < n; e += step) new_data[(first + e) * CHUNKS + L] = old_data[(int64_t)list[e] * CHUNKS + L];
     }
-    __device__ void empty(int64_t v) const { out[v] = -1; }
+};
+
+// Old-grid coordinate of new voxel j (FP64, same operation order as the
+// definition): ((j + 0.5) N_old / N_new) - 0.5, clamped to [0, N_old - 1].
+__device__ inline void upsample_coord(int j, int n_old, int n_new, int &i0, double &f) {
+    double g = ((double)j + 0.5) * (double)n_old / (double)n_new - 0.5;
+    if (g < 0.0) g = 0.0;
+    if (g > (double)(n_old - 1)) g = (double)(n_old - 1);
+    int c = (int)floor(g);
+    if (c > n_old - 2) c = n_old - 2;
+    if (c < 0) c = 0;
+    i0 = c;
+    f = g - (double)c;
+}
+
+// Trilinear values in FP64.  The thread that writes a cell's index entry finds
+// its lower corner and fractions, once for the record's 8 lanes; these hold
+// slots 4L..4L+3 each and the id of one corner for all of them.
+template <int DT>
+struct UpsampleWriter {
+    static constexpr bool kRecords = true;
+    // A tile's records are made in turn, 32 at a time, so small tiles: 16, 4 and
+    // 2 cells a thread took 830, 562 and 469 us for the 6.1M records of
+    // 512x512x128 cells, 18% of them occupied in clusters.
+    static constexpr int kItems = 2;
+    struct Item {
+        int64_t corner;  // the lower corner's place in the old index
+        double f[3];
+    };
+    GridDev go;
+    ParentPred pred;
+    void *new_data;
+    __device__ Item item(int64_t v, int) const {
+        int x[3], c[3];
+        Item it;
+        pred.decode(v, x[0], x[1], x[2]);
+        upsample_coord(x[0], go.nx, pred.nn[0], c[0], it.f[0]);
+        upsample_coord(x[1], go.ny, pred.nn[1], c[1], it.f[1]);
+        upsample_coord(x[2], go.nz, pred.nn[2], c[2], it.f[2]);
+        it.corner = ((int64_t)c[0] * go.ny + c[1]) * go.nz + c[2];
+        return it;
+    }
+    __device__ void records(const Item *list, int n, int64_t first) const {
+        const int L = threadIdx.x & 7;
+        const int64_t my_corner = ((int64_t)(L >> 2) * go.ny + (L >> 1 & 1)) * go.nz + (L & 1);
+        for (int e = threadIdx.x >> 3; e < n; e += kScanThreads / 8) {
+            const Item it = list[e];
+            const double fx = it.f[0], fy = it.f[1], fz = it.f[2];
+            const int my = go.index[it.corner + my_corner];
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            int id[8];
+            typename Rec<DT>::Raw raw[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                id[q] = __shfl(my, q, 8);
+                raw[q] = Rec<DT>::raw(go.data, id[q] < 0 ? 0 : id[q], L);  // the parent's record exists
+            }
+            auto add = [&](int q) {
+                const double w = (q & 4 ? fx : 1.0 - fx) * (q & 2 ? fy : 1.0 - fy) * (q & 1 ? fz : 1.0 - fz);
+                const float4 v = Rec<DT>::cvt(raw[q], L);
+                acc[0] += w * (double)v.x;
+                acc[1] += w * (double)v.y;
+                acc[2] += w * (double)v.z;
+                acc[3] += w * (double)v.w;
+            };
+            if (__all(my >= 0)) {  // no NULL corner in the wave's records
+#pragma unroll
+                for (int q = 0; q < 8; ++q) add(q);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (id[q] >= 0) add(q);
+            }
+            float o[4] = {(float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]};
+            if (L == 6) o[3] = 0.0f;                  // slot 27 is unused,
+            if (L == 7) o[1] = o[2] = o[3] = 0.0f;    // as are those after the density
+            const int64_t m = first + e;
+            if (DT == PLX_F32) {
+                reinterpret_cast<float4 *>(static_cast<char *>(new_data) + m * kRecF32Bytes)[L] =
+                    make_float4(o[0], o[1], o[2], o[3]);
+            } else {
+                uint2 w;
+                if (L == 7) {
+                    w.x = __float_as_uint(o[0]);
+                    w.y = 0u;
+                } else {
+                    w.x = to16<DT>(o[0]) | (to16<DT>(o[1]) << 16);
+                    w.y = to16<DT>(o[2]) | (to16<DT>(o[3]) << 16);
+                    if (L == 6) w.y &= 0xffffu;
+                }
+                reinterpret_cast<uint2 *>(static_cast<char *>(new_data) + m * kRec16Bytes)[L] = w;
+            }
+        }
+    }
 };
 
 // ---- small kernels
@@ -324,189 +537,199 @@ __global__ void unpack_kernel(int64_t n, const void *rec, float *density, float 
     }
 }
 
-// Cell occupancy bits in brick-major order: thread t is bit t of the bitmap,
-// i.e. brick t/512, cell (t%512)/64, (t/8)%8, t%8 inside it; 32-bit words are
-// assembled by ballot.  Cells outside the lattice (partial bricks) get 0.
-__global__ void occupancy_kernel(GridDev g, int64_t nbits, uint32_t *occ) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool bit = false;
-    if (t < nbits) {
-        const int64_t b = t >> 9;
-        const int l = (int)(t & 511);
-        const int bk = (int)(b % g.bz);
-        const int bj = (int)((b / g.bz) % g.by);
-        const int bi = (int)(b / ((int64_t)g.bz * g.by));
-        const int i = bi * PLX_BRICK + (l >> 6), j = bj * PLX_BRICK + ((l >> 3) & 7),
-                  k = bk * PLX_BRICK + (l & 7);
-        if (i < g.nx - 1 && j < g.ny - 1 && k < g.nz - 1) {
-            const int64_t sy = g.nz, sx = (int64_t)g.ny * g.nz;
-            const int32_t *p = g.index + ((int64_t)i * g.ny + j) * g.nz + k;
-            // NULL entries are negative, table ids are not: the cell is empty
-            // exactly when the AND of all eight entries is negative
-            bit = (p[0] & p[1] & p[sy] & p[sy + 1] & p[sx] & p[sx + 1] & p[sx + sy] &
-                   p[sx + sy + 1]) >= 0;
-        }
+// Cell occupancy bits in brick-major order (bit t of brick b is its cell t/64,
+// (t/8)%8, t%8; cells outside the lattice, of partial bricks, get 0) and the
+// seed of the brick's distance, 0 when any of its bits is set, else far.  One
+// wave per brick: the 9x9 rows of 9 index entries that its cells' corners
+// share become one bit each (16 lanes a row, four rows at a time), and lane (i, j) combines four
+// rows into a byte.  A thread per cell, which read all eight corners and
+// divided by the extents, took 150 us for 512x512x128 and 256x256x128 cells
+// together; so 93.
+__global__ __launch_bounds__(256) void occupancy_kernel(GridDev g, int64_t n_brick, uint8_t *occ,
+                                                        uint8_t *bd) {
+    __shared__ uint16_t rows_sh[4][9 * 12];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t b = (int64_t)blockIdx.x * 4 + w;
+    if (b >= n_brick) return;
+    uint16_t *rows = rows_sh[w];
+    // (as many bricks as 32 bits count would have 2^41 cells)
+    const uint32_t br = (uint32_t)b / (uint32_t)g.bz;
+    const int bk = (int)((uint32_t)b - br * g.bz), bi = (int)(br / (uint32_t)g.by), bj = (int)(br - (uint32_t)bi * g.by);
+    const int kk = lane & 15, jj = lane >> 4, left_i = g.nx - bi * PLX_BRICK;
+    const int left_j = (kk < 9 && bk * PLX_BRICK + kk < g.nz) ? min(9, g.ny - bj * PLX_BRICK) : 0;
+    const int64_t sy = g.nz, sx = sy * g.ny;
+    const int32_t *p = g.index + ((int64_t)bi * sx + bj * sy + bk) * PLX_BRICK;
+    const int64_t off = jj * sy + kk;
+    int32_t id[27];
+#pragma unroll
+    for (int it = 0; it < 27; ++it) {  // entries off the lattice: the brick's first one instead
+        const int i = it / 3, j0 = it % 3 * 4;
+        id[it] = p[i < left_i && j0 + jj < left_j ? i * sx + j0 * sy + off : 0];
     }
-    const unsigned long long m = __ballot(bit);
-    const int lane = threadIdx.x & 63;
-    const int64_t w = (t - lane) >> 5;  // first word of this wave
-    if (lane == 0 && (t - lane) < nbits) occ[w] = (uint32_t)(m & 0xffffffffull);
-    if (lane == 32 && (t - lane) + 32 < nbits) occ[w + 1] = (uint32_t)(m >> 32);
+#pragma unroll
+    for (int it = 0; it < 27; ++it) {
+        const uint64_t m = __ballot(it / 3 < left_i && it % 3 * 4 + jj < left_j && id[it] >= 0);
+        if (kk == 0) rows[it * 4 + jj] = (uint16_t)(m >> (lane & 48));
+    }
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+    const int i = lane >> 3, j = lane & 7;
+    const uint32_t m = rows[i * 12 + j] | rows[i * 12 + j + 1] | rows[i * 12 + j + 12] | rows[i * 12 + j + 13];
+    uint32_t bits = (m | m >> 1) & 0xffu;
+    const int nk = g.nz - 1 - bk * PLX_BRICK;  // cells of the lattice along k
+    if (nk < PLX_BRICK) bits &= (1u << nk) - 1u;
+    if (bi * PLX_BRICK + i >= g.nx - 1 || bj * PLX_BRICK + j >= g.ny - 1) bits = 0u;
+    occ[b * 64 + lane] = (uint8_t)bits;
+    const uint64_t any = __ballot(bits != 0u);
+    if (lane == 0) bd[b] = any ? 0 : 255;
 }
 
-// Brick seed: 0 when any cell of the brick has its occupancy bit, else far.
-__global__ void brick_seed_kernel(GridDev g, uint8_t *bd) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nb = (int64_t)g.bx * g.by * g.bz;
-    if (b >= nb) return;
-    uint32_t any = 0u;
-    for (int w = 0; w < 16; ++w) any |= g.occ[b * 16 + w];
-    bd[b] = any ? 0 : 255;
-}
+// Chebyshev distance over bricks, one axis: d(p) <- min over q of max(|p - q|,
+// d(q)) along every line of that axis, capped; z, y and x in turn give the
+// distance in the three-dimensional maximum norm (three launches instead of
+// one relaxation pass per unit of the cap: 174 us to 28 for the bricks
+// of 512x512x128 and 256x256x128 cells).  In place: a workgroup owns 8 lines and
+// walks them 64 bricks at a time, keeping the old values behind it in LDS.
+constexpr int kDistLines = 8, kDistRun = 64, kDistWin = kDistRun + 2 * PLX_BRICK_DIST_CAP;
 
-// One relaxation pass of the Chebyshev distance over bricks, in place:
-// d <- min(d, 1 + min over the 26 neighbours).  Every value stays an upper
-// bound of the true distance; `last` clamps to the cap, which turns the
-// values of unconverged (far) bricks into lower bounds.
-__global__ void brick_dist_pass_kernel(GridDev g, uint8_t *bd, int last) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nb = (int64_t)g.bx * g.by * g.bz;
-    if (b >= nb) return;
-    const int bk = (int)(b % g.bz);
-    const int bj = (int)((b / g.bz) % g.by);
-    const int bi = (int)(b / ((int64_t)g.bz * g.by));
-    int d = bd[b];
-    for (int a = -1; a <= 1; ++a) {
-        const int ii = bi + a;
-        if (ii < 0 || ii >= g.bx) continue;
-        for (int c = -1; c <= 1; ++c) {
-            const int jj = bj + c;
-            if (jj < 0 || jj >= g.by) continue;
-            for (int e = -1; e <= 1; ++e) {
-                const int kk = bk + e;
-                if (kk < 0 || kk >= g.bz) continue;
-                const int nd = bd[((int64_t)ii * g.by + jj) * g.bz + kk] + 1;
-                d = nd < d ? nd : d;
+__global__ __launch_bounds__(256) void brick_dist_kernel(uint8_t *bd, int64_t n_line, int len,
+                                                         int64_t stride) {
+    __shared__ uint8_t win[kDistWin][kDistLines];
+    constexpr int cap = PLX_BRICK_DIST_CAP;
+    const int ln = threadIdx.x % kDistLines, t = threadIdx.x / kDistLines;
+    constexpr int nt = 256 / kDistLines;
+    const int64_t l = (int64_t)blockIdx.x * kDistLines + ln;
+    uint8_t *line = bd + (l / stride) * (stride * len) + l % stride;
+    const bool live = l < n_line;
+    for (int p0 = 0; p0 < len; p0 += kDistRun) {
+        // window rows 0..2cap-1 are rows kDistRun.. of the window before
+        // (rows of the run behind, then the first `cap` of this one)
+        uint8_t keep[2 * cap / nt];
+#pragma unroll
+        for (int u = 0; u < 2 * cap / nt; ++u) {
+            const int r = t + u * nt, p = p0 - cap + r;
+            if (p0 > 0) keep[u] = win[kDistRun + r][ln];
+            else keep[u] = live && p >= 0 && p < len ? line[p * stride] : 255;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2 * cap / nt; ++u) win[t + u * nt][ln] = keep[u];
+        for (int r = 2 * cap + t; r < kDistWin; r += nt) {
+            const int p = p0 - cap + r;
+            win[r][ln] = live && p < len ? line[p * stride] : 255;
+        }
+        __syncthreads();
+        for (int r = cap + t; r < cap + kDistRun; r += nt) {
+            int d = win[r][ln] < cap ? win[r][ln] : cap;
+            for (int o = 1; o < d; ++o) {
+                const int a = win[r - o][ln], c = win[r + o][ln];
+                const int m = a < c ? a : c, x = m > o ? m : o;
+                d = x < d ? x : d;
             }
+            if (live && p0 + r - cap < len) line[(p0 + r - cap) * stride] = (uint8_t)d;
         }
+        __syncthreads();
     }
-    if (last) d = d < PLX_BRICK_DIST_CAP ? d : PLX_BRICK_DIST_CAP;
-    bd[b] = (uint8_t)d;
 }
 
+// Occupied and stored cells as one bit each, 32 cells a word: bits[0 ..
+// 2 nw64) and the same number of words after them (nw64 = 64-cell words).
+// Occupied: a voxel with density (value == NULL) or value[id] >= thresh.
 template <int DT>
-__global__ void prune_occ_kernel(GridDev g, int64_t ncell, float thresh, uint8_t *occ8) {
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= ncell) return;
-    int32_t id = g.index[v];
-    occ8[v] = (id >= 0 && rec_sigma<DT>(g.data, id) >= thresh) ? 1 : 0;
-}
-
-__global__ void prune_occ_value_kernel(GridDev g, int64_t ncell, const float *value, float thresh,
-                                      uint8_t *occ8) {
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= ncell) return;
-    int32_t id = g.index[v];
-    occ8[v] = (id >= 0 && value[id] >= thresh) ? 1 : 0;
-}
-
-__global__ __launch_bounds__(kCountThreads) void prune_keep_kernel(GridDev g, int64_t ncell,
-                                                                   const uint8_t *occ8, uint8_t *keep,
-                                                                   unsigned long long *counts) {
-    const int64_t stride = (int64_t)gridDim.x * kCountThreads;
-    unsigned long long n_kept = 0, n_nonnull = 0;
-    for (int64_t v = (int64_t)blockIdx.x * kCountThreads + threadIdx.x; v < ncell; v += stride) {
-        bool nonnull = false, kept = false;
-        int k = (int)(v % g.nz);
-        int64_t r = v / g.nz;
-        int j = (int)(r % g.ny);
-        int i = (int)(r / g.ny);
-        nonnull = g.index[v] >= 0;
-        if (nonnull) {
-            for (int a = -1; a <= 1 && !kept; ++a) {
-                int ii = i + a;
-                if (ii < 0 || ii >= g.nx) continue;
-                for (int b = -1; b <= 1 && !kept; ++b) {
-                    int jj = j + b;
-                    if (jj < 0 || jj >= g.ny) continue;
-                    for (int c = -1; c <= 1; ++c) {
-                        int kk = k + c;
-                        if (kk < 0 || kk >= g.nz) continue;
-                        if (occ8[((int64_t)ii * g.ny + jj) * g.nz + kk]) {
-                            kept = true;
-                            break;
-                        }
-                    }
-                }
-            }
-        }
-        keep[v] = kept ? 1 : 0;
-        n_kept += kept;
-        n_nonnull += nonnull;
+__global__ __launch_bounds__(256) void prune_bits_kernel(GridDev g, int64_t ncell, const float *value,
+                                                         float thresh, unsigned long long *bits) {
+    constexpr int kCells = 4;  // per thread, their reads in flight together
+    const int lane = threadIdx.x & 63;
+    const int64_t nw = (ncell + 63) / 64, w0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kCells;
+    int32_t id[kCells];
+    float x[kCells];
+#pragma unroll
+    for (int u = 0; u < kCells; ++u) {
+        const int64_t v = (w0 + u) * 64 + lane;
+        id[u] = v < ncell ? g.index[v] : -1;
     }
-    block_add2(n_kept, n_nonnull, counts);
+#pragma unroll
+    for (int u = 0; u < kCells; ++u)
+        x[u] = id[u] < 0 ? 0.0f : value ? value[id[u]] : rec_sigma<DT>(g.data, id[u]);
+#pragma unroll
+    for (int u = 0; u < kCells; ++u) {
+        const uint64_t stored = __ballot(id[u] >= 0), occ = __ballot(id[u] >= 0 && x[u] >= thresh);
+        if (lane == 0 && w0 + u < nw) {
+            bits[w0 + u] = occ;
+            bits[nw + w0 + u] = stored;
+        }
+    }
+}
+
+// 34 bits of a bit string of n words from bit b on (b >= -1; bits before and
+// after the string are 0).
+__device__ inline uint64_t bits34(const uint32_t *w, int64_t n, int64_t b) {
+    const int64_t i = b >> 5;  // floor
+    const int s = (int)(b & 31);
+    const uint64_t a = i >= 0 && i < n ? w[i] : 0u, c = i + 1 < n ? w[i + 1] : 0u, d = i + 2 < n ? w[i + 2] : 0u;
+    uint64_t x = (a | c << 32) >> s;
+    if (s > 30) x |= d << (64 - s);
+    return x & 0x3ffffffffull;
+}
+
+// keep = stored with an occupied voxel in the 3x3x3 neighbourhood, for 32
+// cells of a row at a time: the nine rows' bits, unaligned, ORed and spread by
+// one cell.  Reading 27 bytes for every cell took 207 us for 256x256x128
+// cells; so 31.
+__global__ __launch_bounds__(kCountThreads) void prune_keep_kernel(GridDev g, int64_t ncell,
+                                                                   const uint32_t *bits, uint8_t *keep,
+                                                                   unsigned long long *counts) {
+    __shared__ uint32_t word_sh[kCountThreads];
+    __shared__ int64_t cell_sh[kCountThreads];
+    __shared__ uint8_t cells_sh[kCountThreads];
+    const int64_t nw = 2 * ((ncell + 63) / 64);
+    const int per_row = (g.nz + 31) / 32;
+    const int64_t n_grp = (int64_t)g.nx * g.ny * per_row;
+    unsigned long long n_kept = 0, n_stored = 0;
+    for (int64_t g0 = (int64_t)blockIdx.x * kCountThreads; g0 < n_grp; g0 += (int64_t)gridDim.x * kCountThreads) {
+        const int64_t grp = g0 + threadIdx.x;
+        uint32_t kept = 0u;
+        int64_t cell = 0;
+        int cells = 0;
+        if (grp < n_grp) {
+            const int k0 = (int)(grp % per_row) * 32;
+            const int64_t r = grp / per_row;
+            const int j = (int)(r % g.ny), i = (int)(r / g.ny);
+            uint64_t near = 0;
+            for (int a = -1; a <= 1; ++a)
+                for (int c = -1; c <= 1; ++c)
+                    if (i + a >= 0 && i + a < g.nx && j + c >= 0 && j + c < g.ny)
+                        near |= bits34(bits, nw, (r + (int64_t)a * g.ny + c) * g.nz + k0 - 1);
+            if (k0 == 0) near &= ~1ull;  // the row's own cells only
+            const int left = g.nz - k0;
+            if (left < 33) near &= (1ull << (left + 1)) - 1;
+            uint32_t stored = (uint32_t)(bits34(bits + nw, nw, r * g.nz + k0 - 1) >> 1);
+            if (left < 32) stored &= (1u << left) - 1u;
+            kept = (uint32_t)(near | near >> 1 | near >> 2) & stored;
+            n_kept += __popc(kept);
+            n_stored += __popc(stored);
+            cell = r * g.nz + k0;
+            cells = left < 32 ? left : 32;
+        }
+        __syncthreads();  // the words before are written
+        word_sh[threadIdx.x] = kept;
+        cell_sh[threadIdx.x] = cell;
+        cells_sh[threadIdx.x] = (uint8_t)cells;
+        __syncthreads();
+#pragma unroll 4
+        for (int c = threadIdx.x; c < kCountThreads * 32; c += kCountThreads)
+            if (c % 32 < cells_sh[c / 32]) keep[cell_sh[c / 32] + c % 32] = word_sh[c / 32] >> (c % 32) & 1u;
+    }
+    block_add2(n_kept, n_stored, counts);
 }
 
 __global__ __launch_bounds__(kCountThreads) void upsample_count_kernel(ParentPred pred, int64_t n,
                                                                        unsigned long long *out) {
-    const int64_t stride = (int64_t)gridDim.x * kCountThreads;
     unsigned long long c = 0;
-    for (int64_t v = (int64_t)blockIdx.x * kCountThreads + threadIdx.x; v < n; v += stride)
-        c += pred(v) ? 1 : 0;
+    for (int64_t v = ((int64_t)blockIdx.x * kCountThreads + threadIdx.x) * kScanItems; v < n;
+         v += (int64_t)gridDim.x * kCountThreads * kScanItems)
+        c += __popc(pred.flags<kScanItems>(v, n));
     block_add(c, out);
-}
-
-// Old-grid coordinate of new voxel j (FP64, same operation order as the
-// definition): ((j + 0.5) N_old / N_new) - 0.5, clamped to [0, N_old - 1].
-__device__ inline void upsample_coord(int j, int n_old, int n_new, int &i0, double &f) {
-    double g = ((double)j + 0.5) * (double)n_old / (double)n_new - 0.5;
-    if (g < 0.0) g = 0.0;
-    if (g > (double)(n_old - 1)) g = (double)(n_old - 1);
-    int c = (int)floor(g);
-    if (c > n_old - 2) c = n_old - 2;
-    if (c < 0) c = 0;
-    i0 = c;
-    f = g - (double)c;
-}
-
-template <int DT>
-__global__ void upsample_values_kernel(GridDev go, const int32_t *new_index, int nn0, int nn1,
-                                       int nn2, int64_t ncell_new, void *new_data) {
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= ncell_new) return;
-    int32_t nid = new_index[v];
-    if (nid < 0) return;
-    int k = (int)(v % nn2);
-    int64_t r = v / nn2;
-    int j = (int)(r % nn1);
-    int i = (int)(r / nn1);
-    int c0[3];
-    double f[3];
-    upsample_coord(i, go.nx, nn0, c0[0], f[0]);
-    upsample_coord(j, go.ny, nn1, c0[1], f[1]);
-    upsample_coord(k, go.nz, nn2, c0[2], f[2]);
-    double acc[29];
-    for (int s = 0; s < 29; ++s) acc[s] = 0.0;
-    for (int c = 0; c < 8; ++c) {
-        int dx = (c >> 2) & 1, dy = (c >> 1) & 1, dz = c & 1;
-        double w = (dx ? f[0] : 1.0 - f[0]) * (dy ? f[1] : 1.0 - f[1]) * (dz ? f[2] : 1.0 - f[2]);
-        int64_t id = go.index[((int64_t)(c0[0] + dx) * go.ny + (c0[1] + dy)) * go.nz + (c0[2] + dz)];
-        if (id < 0) continue;
-        for (int s = 0; s < PLX_NSH; ++s) acc[s] += w * (double)rec_slot<DT>(go.data, id, s);
-        acc[PLX_SLOT_SIGMA] += w * (double)rec_sigma<DT>(go.data, id);
-    }
-    if (DT == PLX_F32) {
-        float *o = reinterpret_cast<float *>(static_cast<char *>(new_data) + (int64_t)nid * kRecF32Bytes);
-        for (int s = 0; s < 32; ++s)
-            o[s] = (s < PLX_NSH || s == PLX_SLOT_SIGMA) ? (float)acc[s] : 0.0f;
-    } else {
-        char *o = static_cast<char *>(new_data) + (int64_t)nid * kRec16Bytes;
-        unsigned short *h = reinterpret_cast<unsigned short *>(o);
-        for (int s = 0; s < 28; ++s) h[s] = s < PLX_NSH ? (unsigned short)to16<DT>((float)acc[s]) : 0;
-        float *sg = reinterpret_cast<float *>(o + 56);
-        sg[0] = (float)acc[PLX_SLOT_SIGMA];
-        sg[1] = 0.0f;
-    }
 }
 
 template <int DS, int DD>
@@ -546,6 +769,19 @@ int sync_read_u64(const unsigned long long *dev, int n, int64_t *host, hipStream
 
 inline unsigned blocks_for(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
+MaskPred mask_pred(const uint8_t *mask) {
+    return {mask, reinterpret_cast<uintptr_t>(mask) % 16 == 0};
+}
+
+ParentPred parent_pred(const plx_grid *grid, const int32_t new_reso[3]) {
+    ParentPred p{grid->index, {}, {}, n_cells(new_reso) < (1ll << 32)};
+    for (int a = 0; a < 3; ++a) {
+        p.on[a] = grid->reso[a];
+        p.nn[a] = new_reso[a];
+        p.narrow = p.narrow && 2 * (uint64_t)new_reso[a] * (uint64_t)grid->reso[a] < (1ull << 32);
+    }
+    return p;
+}
 
 // Shared by both prune counts: occupied = non-NULL with density (value ==
 // NULL) or value[id] at least thresh; kept = non-NULL with an occupied voxel
@@ -561,18 +797,14 @@ int prune_count(const plx_grid *grid, const float *value, float thresh, uint8_t 
     const WsLayout l = ws_layout(ncell);
     if ((rc = check_ws(ws, ws_bytes, l.bytes, fn))) return rc;
     auto *counts = static_cast<unsigned long long *>(ws);
-    uint8_t *occ8 = static_cast<uint8_t *>(ws) + l.bytes8;
+    auto *bits = reinterpret_cast<unsigned long long *>(static_cast<char *>(ws) + l.bytes8);
     if ((rc = zero_counters(ws, s, fn))) return rc;
     GridDev g = to_dev(grid);
-    unsigned nb = blocks_for(ncell, 256);
-    if (value) {
-        prune_occ_value_kernel<<<nb, 256, 0, s>>>(g, ncell, value, thresh, occ8);
-    } else {
-        PLX_DISPATCH_DT(grid->sh_dtype, DT,
-                        prune_occ_kernel<DT><<<nb, 256, 0, s>>>(g, ncell, thresh, occ8));
-    }
+    PLX_DISPATCH_DT(grid->sh_dtype, DT,
+                    prune_bits_kernel<DT><<<blocks_for(ncell, 1024), 256, 0, s>>>(g, ncell, value, thresh, bits));
     if ((rc = check_launch(fn))) return rc;
-    prune_keep_kernel<<<count_blocks(ncell), kCountThreads, 0, s>>>(g, ncell, occ8, keep_out, counts);
+    prune_keep_kernel<<<count_blocks(ncell), kCountThreads, 0, s>>>(g, ncell, reinterpret_cast<const uint32_t *>(bits),
+                                                                         keep_out, counts);
     if ((rc = check_launch(fn))) return rc;
     int64_t h[2];
     if ((rc = sync_read_u64(counts, 2, h, s, fn))) return rc;
@@ -620,7 +852,7 @@ int plx_grid_create(const uint8_t *mask, const int32_t reso[3], int32_t *index_o
     int64_t n = n_cells(reso);
     int rc = check_ws(ws, ws_bytes, ws_layout(n).bytes, "plx_grid_create");
     if (rc) return rc;
-    return run_scan(MaskPred{mask}, IndexWriter{index_out}, n, ws, as_stream(stream), "plx_grid_create");
+    return run_scan(mask_pred(mask), IndexWriter{}, n, index_out, ws, as_stream(stream), "plx_grid_create");
 }
 
 int plx_records_pack(int32_t sh_dtype, int64_t n, const float *density, const float *sh,
@@ -664,21 +896,20 @@ int plx_grid_build_occupancy(const plx_grid *grid, uint32_t *occ_out, plx_stream
     if (rc) return rc;
     if (!occ_out) return fail(PLX_EINVAL, "plx_grid_build_occupancy: occ_out is NULL");
     hipStream_t s = as_stream(stream);
-    // bits are whole bricks of 512, so whole waves: every word is written by
-    // the wave that owns it
-    const int64_t nbits = occ_words(grid->reso) * 32;
     plx_grid gd = *grid;
     gd.occ = occ_out;
     GridDev g = to_dev(&gd);
-    occupancy_kernel<<<blocks_for(nbits, 256), 256, 0, s>>>(g, nbits, occ_out);
-    if ((rc = check_launch("plx_grid_build_occupancy"))) return rc;
     uint8_t *bd = reinterpret_cast<uint8_t *>(occ_out) + occ_brick_offset(grid->reso);
     const int64_t nb = n_bricks(grid->reso);
-    brick_seed_kernel<<<blocks_for(nb, 256), 256, 0, s>>>(g, bd);
+    occupancy_kernel<<<blocks_for(nb, 4), 256, 0, s>>>(g, nb, reinterpret_cast<uint8_t *>(occ_out), bd);
     if ((rc = check_launch("plx_grid_build_occupancy"))) return rc;
-    for (int p = 0; p < PLX_BRICK_DIST_CAP; ++p) {
-        brick_dist_pass_kernel<<<blocks_for(nb, 256), 256, 0, s>>>(g, bd, p == PLX_BRICK_DIST_CAP - 1);
+    const int len[3] = {g.bz, g.by, g.bx};
+    int64_t stride = 1;
+    for (int a = 0; a < 3; ++a) {
+        const int64_t lines = nb / len[a];
+        brick_dist_kernel<<<blocks_for(lines, kDistLines), 256, 0, s>>>(bd, lines, len[a], stride);
         if ((rc = check_launch("plx_grid_build_occupancy"))) return rc;
+        stride *= len[a];
     }
     return PLX_OK;
 }
@@ -708,11 +939,15 @@ int plx_grid_prune_apply(const plx_grid *grid, const uint8_t *keep, plx_grid *ou
     if (out->sh_dtype != grid->sh_dtype)
         return fail(PLX_EINVAL, "plx_grid_prune_apply: out->sh_dtype differs");
     if (out->n_vox > 0 && !out->data) return fail(PLX_EINVAL, "plx_grid_prune_apply: out->data is NULL");
-    int chunks = (int)(plx_record_bytes(grid->sh_dtype) / 16);
-    PruneWriter w{const_cast<int32_t *>(out->index), grid->index, static_cast<const uint4 *>(grid->data),
-                  static_cast<uint4 *>(out->data), chunks};
     if ((rc = check_ws(ws, ws_bytes, ws_layout(n_cells(grid->reso)).bytes, "plx_grid_prune_apply"))) return rc;
-    return run_scan(MaskPred{keep}, w, n_cells(grid->reso), ws, as_stream(stream), "plx_grid_prune_apply");
+    auto run = [&](auto writer) {
+        return run_scan(mask_pred(keep), writer, n_cells(grid->reso), const_cast<int32_t *>(out->index), ws,
+                        as_stream(stream), "plx_grid_prune_apply");
+    };
+    const auto *src = static_cast<const uint4 *>(grid->data);
+    auto *dst = static_cast<uint4 *>(const_cast<void *>(static_cast<const void *>(out->data)));
+    if (grid->sh_dtype == PLX_F32) return run(PruneWriter<kRecF32Bytes / 16>{grid->index, src, dst});
+    return run(PruneWriter<kRec16Bytes / 16>{grid->index, src, dst});
 }
 
 int plx_grid_upsample_count(const plx_grid *grid, const int32_t new_reso[3], void *ws,
@@ -723,13 +958,12 @@ int plx_grid_upsample_count(const plx_grid *grid, const int32_t new_reso[3], voi
     for (int a = 0; a < 3; ++a)
         if (new_reso[a] < 2) return fail(PLX_EINVAL, "plx_grid_upsample_count: new_reso[%d] < 2", a);
     hipStream_t s = as_stream(stream);
-    ParentPred pred{grid->index, {grid->reso[0], grid->reso[1], grid->reso[2]},
-                    {new_reso[0], new_reso[1], new_reso[2]}};
+    const ParentPred pred = parent_pred(grid, new_reso);
     int64_t n = n_cells(new_reso);
     if ((rc = check_ws(ws, ws_bytes, PLX_COUNT_WORKSPACE_BYTES, "plx_grid_upsample_count"))) return rc;
     auto *cnt = static_cast<unsigned long long *>(ws);
     if ((rc = zero_counters(ws, s, "plx_grid_upsample_count"))) return rc;
-    upsample_count_kernel<<<count_blocks(n), kCountThreads, 0, s>>>(pred, n, cnt);
+    upsample_count_kernel<<<count_blocks((n + kScanItems - 1) / kScanItems), kCountThreads, 0, s>>>(pred, n, cnt);
     if ((rc = check_launch("plx_grid_upsample_count"))) return rc;
     return sync_read_u64(cnt, 1, n_out, s, "plx_grid_upsample_count");
 }
@@ -745,18 +979,14 @@ int plx_grid_upsample_apply(const plx_grid *grid, plx_grid *out, void *ws, int64
         return fail(PLX_EINVAL, "plx_grid_upsample_apply: out->sh_dtype differs from grid->sh_dtype");
     if (out->n_vox > 0 && !out->data) return fail(PLX_EINVAL, "plx_grid_upsample_apply: out->data is NULL");
     hipStream_t s = as_stream(stream);
-    ParentPred pred{grid->index, {grid->reso[0], grid->reso[1], grid->reso[2]},
-                    {out->reso[0], out->reso[1], out->reso[2]}};
+    const ParentPred pred = parent_pred(grid, out->reso);
     int64_t n = n_cells(out->reso);
     if ((rc = check_ws(ws, ws_bytes, ws_layout(n).bytes, "plx_grid_upsample_apply"))) return rc;
-    if ((rc = run_scan(pred, IndexWriter{const_cast<int32_t *>(out->index)}, n, ws, s,
-                       "plx_grid_upsample_apply")))
-        return rc;
     GridDev g = to_dev(grid);
     PLX_DISPATCH_DT(grid->sh_dtype, DT,
-                    upsample_values_kernel<DT><<<blocks_for(n, 256), 256, 0, s>>>(
-                        g, out->index, out->reso[0], out->reso[1], out->reso[2], n, out->data));
-    return check_launch("plx_grid_upsample_apply");
+                    return run_scan<UpsampleWriter<DT>::kItems>(pred, UpsampleWriter<DT>{g, pred, const_cast<void *>(out->data)},
+                                    n, const_cast<int32_t *>(out->index), ws, s, "plx_grid_upsample_apply"));
+    return PLX_OK;
 }
 
 int plx_touched_count(const uint8_t *touched, int64_t n_vox, void *ws, int64_t ws_bytes,

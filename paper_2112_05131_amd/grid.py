@@ -9,11 +9,12 @@ from . import binding as B
 
 
 def _alloc_records(n: int, sh_dtype: int, device) -> torch.Tensor:
-    """[n, 32] float32 (128-byte records) or [n, 32] int16 (64-byte records)."""
+    """[n, 32] float32 (128-byte records) or [n, 32] int16 (64-byte records),
+    for a call that writes every slot of every record."""
     n = max(int(n), 0)
     if sh_dtype == B.PLX_F32:
-        return torch.zeros(n, B.REC_SLOTS, dtype=torch.float32, device=device)
-    return torch.zeros(n, B.REC_SLOTS, dtype=torch.int16, device=device)
+        return torch.empty(n, B.REC_SLOTS, dtype=torch.float32, device=device)
+    return torch.empty(n, B.REC_SLOTS, dtype=torch.int16, device=device)
 
 
 class Grid:
