@@ -84,7 +84,7 @@ __device__ __forceinline__ void update(int64_t m, int L, void *data, float *mast
         const int s = 4 * L + e;
         if (s < PLX_NSH || s == PLX_SLOT_SIGMA) {
             const float lr = s == PLX_SLOT_SIGMA ? lr_sigma : lr_sh;
-            v[e] = beta * v[e] + (1.0f - beta) * g[e] * g[e];
+            v[e] = fmaf(beta, v[e], (1.0f - beta) * g[e] * g[e]);
             p[e] = p[e] - lr * g[e] / (sqrtf(v[e]) + eps);
         }
     }
