@@ -173,6 +173,15 @@ struct Sample {
     float delta;   // interval length
 };
 
+// Interval length of sample k alone.
+__device__ inline float sample_delta(const GridDev &g, float t_near, float t_far, int k) {
+#pragma clang fp contract(off)
+    float kk = (float)k * g.step;
+    float t = t_near + kk;
+    float rest = t_far - t;
+    return rest < g.step ? rest : g.step;
+}
+
 __device__ inline Sample sample_at(const GridDev &g, const RayGeom &r, int k) {
 #pragma clang fp contract(off)
     Sample s;
@@ -191,8 +200,7 @@ __device__ inline Sample sample_at(const GridDev &g, const RayGeom &r, int k) {
         s.cell[a] = i0;
         s.f[a] = f;
     }
-    float rest = r.t_far - t;
-    s.delta = rest < g.step ? rest : g.step;
+    s.delta = sample_delta(g, r.t_near, r.t_far, k);
     return s;
 }
 

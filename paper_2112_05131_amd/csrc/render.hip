@@ -1600,18 +1600,25 @@ void seg_bwd_kernel(GridDev g, BinArgs a) {
 // through the trilinear weights and the SH basis); only the order of the
 // additions differs.
 
+// Its phases are short and latency shows between them (two workgroups a CU,
+// 1,100 samples each on 1M rays through 512^3): so no long chain runs on the
+// few lanes that own a segment -- exponentials, weights and gradients are
+// found by the lane that has the sample, and a segment's lane only subtracts
+// depths and sums g . R -- and only the brick's stored voxels are given
+// lanes, in one round where a brick of mostly empty corners took two.
+// 2.24 -> 2.07 ms; about 1.07 are its 21M 64-byte atomic requests (20 G/s).
+
 constexpr int kScatterThreads = 512;       // threads of a scatter workgroup
 constexpr int kScatterSegs = 256;          // segments per pass
 constexpr int kVoxRounds = (kBrickVox + kScatterThreads - 1) / kScatterThreads;
 constexpr int kScatterCap = 1536;          // samples in LDS per pass
 constexpr int kScatterPer = kScatterCap / kScatterThreads;
+constexpr int kChainU = 4;                 // chain steps whose LDS reads are issued together
 constexpr int kStageRows = 8;              // rows a wave stages per flush round
 constexpr int kStageStride = 29;           // 28 values and the voxel id per staged row
 
-// A sample in the scatter's LDS.  Before the sort: v = the interpolated
-// values, then (after the recurrence) the gradients; code = sample index and
-// cell.  After the sort: f, the gradients in v, and seg = the pass-local
-// number of its segment.
+// A sample in the scatter's LDS, sorted by cell: its position in the cell, the
+// gradients of its values and the pass-local number of its segment.
 struct LdsSample {
     float f[3];
     float v[4];
@@ -1661,11 +1668,18 @@ __device__ __forceinline__ void flush_voxel_rows(float *stage, const float acc[2
 // Reverse recurrence of one segment (the state a lane carries along it).
 struct SegState {
     double tau_after;  // optical depth after the current sample
-    float T_after;
     float gR;          // g . (radiance collected after the current sample)
-    float gr[3];       // dL/dC of the ray
-    float ls;          // Cauchy prior loss of the lane
 };
+
+// What the samples of a segment read while the pass's gradients are formed;
+// the flush stages its rows in the same LDS afterwards.
+struct SegParts {
+    float4 g[kScatterSegs];     // dL/dC of the ray; w: t_near
+    float t_far[kScatterSegs];
+    float tau[kScatterSegs];    // optical depth after the segment's last sample of the pass
+};
+constexpr int kStageFloats = kScatterThreads / kWave * kStageRows * kStageStride;
+static_assert(sizeof(SegParts) <= kStageFloats * sizeof(float), "the parts fit the staging rows");
 
 template <bool CAUCHY>
 __global__ __launch_bounds__(kScatterThreads) __attribute__((amdgpu_waves_per_eu(4)))
@@ -1676,28 +1690,41 @@ void seg_scatter_kernel(GridDev g, BinArgs a) {
     __shared__ int s_cnt[kBrickCells];         // samples per cell
     __shared__ int s_coff[kBrickCells + 1];    // first sorted position of each cell
     __shared__ __align__(16) LdsSample s_rec[kScatterCap];   // the pass's samples
-    __shared__ float s_stage[kScatterThreads / kWave * kStageRows * kStageStride];
+    __shared__ __align__(16) float s_stage[kStageFloats];
+    __shared__ int s_vid[kBrickVox];           // the brick's stored corner voxels: id
+    __shared__ uint16_t s_vpos[kBrickVox];     // and position x*81 + y*9 + z in the 9^3 lattice
 
     if (blockIdx.x >= (unsigned)a.n_brick) return;
     const int t = threadIdx.x;
     float *s_y = reinterpret_cast<float *>(s_y4);
     float *stage = s_stage + (t / kWave) * kStageRows * kStageStride;
+    SegParts &parts = *reinterpret_cast<SegParts *>(s_stage);
+    // per sample of the pass, before the sort: optical thickness, then the
+    // depth before the sample; its weight, then g . R after it; its g . colour
+    float *s_tau = reinterpret_cast<float *>(s_rec), *s_w = s_tau + kScatterCap, *s_gc = s_w + kScatterCap;
     const int64_t jo = a.blist[blockIdx.x];
     int bxyz[3];
     brick_at(g, jo, bxyz);
     const int64_t seg0 = a.boff[jo * kLenClasses], seg1 = a.boff[(jo + 1) * kLenClasses];
 
-    // the lane's corner voxels (position p = x*81 + y*9 + z of the 9^3 lattice)
-    int vid[kVoxRounds];
+    // list the stored corner voxels, in lattice order
+    int n_vox = 0;
 #pragma unroll
     for (int rr = 0; rr < kVoxRounds; ++rr) {
         const int p = t + rr * kScatterThreads;
-        vid[rr] = -1;
+        int id = -1;
         if (p < kBrickVox) {
             const int X = bxyz[0] * PLX_BRICK + p / 81, Y = bxyz[1] * PLX_BRICK + (p / 9) % 9,
                       Z = bxyz[2] * PLX_BRICK + p % 9;
-            if (X < g.nx && Y < g.ny && Z < g.nz) vid[rr] = g.index[((int64_t)X * g.ny + Y) * g.nz + Z];
+            if (X < g.nx && Y < g.ny && Z < g.nz) id = g.index[((int64_t)X * g.ny + Y) * g.nz + Z];
         }
+        int64_t on;
+        const int at = n_vox + (int)block_scan_excl<kScatterThreads>(id >= 0 ? 1 : 0, &on);
+        if (id >= 0) {
+            s_vid[at] = id;
+            s_vpos[at] = (uint16_t)p;
+        }
+        n_vox += (int)on;
     }
     float ls = 0.0f;
 
@@ -1705,28 +1732,34 @@ void seg_scatter_kernel(GridDev g, BinArgs a) {
         // a group of up to kScatterSegs segments; lane t < ns walks segment t
         const int ns = (int)min((int64_t)kScatterSegs, seg1 - c0);
         int occ = 0;
-        int4 sg = make_int4(0, 0, -1, 0);
         SegState st = {};
-        if (t < ns) {
+        // the lane's segment: SH basis and parts to LDS (the flush of a pass
+        // overwrites the parts)
+        auto load_parts = [&](bool first) {
+            if (t >= ns) return;
             const int64_t i = c0 + t;
-            sg = a.bseg[i];
-            float d[3] = {0.f, 0.f, 1.f};
+            const int4 sg = a.bseg[i];
+            float o[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 1.f};
+            float4 gg = make_float4(0.f, 0.f, 0.f, 0.f);
+            RayGeom r = {};
             if (seg_valid(a, sg, a.n_seg)) {
-                occ = a.nocc[i];
-                d[0] = a.rays_d[3 * (int64_t)sg.x];
-                d[1] = a.rays_d[3 * (int64_t)sg.x + 1];
-                d[2] = a.rays_d[3 * (int64_t)sg.x + 2];
-                const float4 gg = a.g_ray[sg.x];
-                st.gr[0] = gg.x;
-                st.gr[1] = gg.y;
-                st.gr[2] = gg.z;
-                st.tau_after = a.tau_in[sg.w] + a.tau_seg[sg.w];
-                st.gR = a.gr_after[sg.w] - gg.w;  // the beta factor joins the running sum
-                st.T_after = expf(-(float)st.tau_after);
+                load_ray_lane(a, sg.x, o, d);
+                gg = a.g_ray[sg.x];
+                (void)ray_setup(g, o, d, r);
+                if (first) {
+                    occ = a.nocc[i];
+                    st.tau_after = a.tau_in[sg.w] + a.tau_seg[sg.w];
+                    st.gR = a.gr_after[sg.w] - gg.w;  // the beta factor joins the running sum
+                }
             }
-            s_soff[t] = a.soff[i];
-            sh_basis_all(d, s_y + t * 12);
-        }
+            parts.g[t] = make_float4(gg.x, gg.y, gg.z, r.t_near);
+            parts.t_far[t] = r.t_far;
+            if (first) {
+                s_soff[t] = a.soff[i];
+                sh_basis_all(d, s_y + t * 12);
+            }
+        };
+        load_parts(true);
         int64_t tot64;
         const int pre = (int)block_scan_excl<kScatterThreads>(occ, &tot64);
         const int tot = (int)tot64;
@@ -1739,15 +1772,20 @@ void seg_scatter_kernel(GridDev g, BinArgs a) {
         for (int q0 = ((tot - 1) / kScatterCap) * kScatterCap; tot > 0 && q0 >= 0; q0 -= kScatterCap) {
             const int nq = min(kScatterCap, tot - q0);
             for (int c = t; c < kBrickCells; c += kScatterThreads) s_cnt[c] = 0;
-            // load the pass's samples (slots first, then all loads), count them
-            // per cell and leave them unsorted in LDS for the recurrence
+            const int e_lo = max(pre, q0) - q0, e_hi = min(pre + occ, q0 + nq) - q0;  // the lane's segment
+            if (q0 + nq < tot) load_parts(false);
+            if (t < ns) parts.tau[t] = (float)st.tau_after;
+            // load the pass's samples (slots first, then all loads)
             int seg_u[kScatterPer];
-            int64_t slot_u[kScatterPer];
+            float4 val_u[kScatterPer];
+            int code_u[kScatterPer];
+            auto slot_of = [&](int u) {
+                return s_soff[seg_u[u]] + (q0 + u * kScatterThreads + t - s_pre[seg_u[u]]);
+            };
 #pragma unroll
             for (int u = 0; u < kScatterPer; ++u) {
                 const int q = u * kScatterThreads + t;
                 seg_u[u] = -1;
-                slot_u[u] = 0;
                 if (q < nq) {
                     const int qq = q0 + q;
                     int lo = 0, hi = ns - 1;  // last segment whose first sample is <= qq
@@ -1757,31 +1795,26 @@ void seg_scatter_kernel(GridDev g, BinArgs a) {
                         else hi = mid - 1;
                     }
                     seg_u[u] = lo;
-                    slot_u[u] = s_soff[lo] + (qq - s_pre[lo]);
                 }
             }
-            SampleRec rec_u[kScatterPer];
-#pragma unroll
-            for (int u = 0; u < kScatterPer; ++u)
-                if (seg_u[u] >= 0) rec_u[u] = a.srec[slot_u[u]];
-            __syncthreads();  // s_cnt cleared; the previous pass's LDS reads done
-            int cell_u[kScatterPer], rank_u[kScatterPer];
 #pragma unroll
             for (int u = 0; u < kScatterPer; ++u) {
-                if (seg_u[u] >= 0) {
-                    const int code = __float_as_int(rec_u[u].pos.w);
-                    cell_u[u] = code & (kBrickCells - 1);
-                    rank_u[u] = atomicAdd(&s_cnt[cell_u[u]], 1);
-                    LdsSample &ls_q = s_rec[u * kScatterThreads + t];
-                    ls_q.f[0] = rec_u[u].pos.x;
-                    ls_q.f[1] = rec_u[u].pos.y;
-                    ls_q.f[2] = rec_u[u].pos.z;
-                    ls_q.v[0] = rec_u[u].val.x;
-                    ls_q.v[1] = rec_u[u].val.y;
-                    ls_q.v[2] = rec_u[u].val.z;
-                    ls_q.v[3] = rec_u[u].val.w;
-                    ls_q.seg = code;
-                }
+                if (seg_u[u] < 0) continue;
+                const SampleRec *rec = a.srec + slot_of(u);
+                val_u[u] = rec->val;
+                code_u[u] = __float_as_int(rec->pos.w);
+            }
+            __syncthreads();  // s_cnt cleared, the parts written; the previous pass's LDS reads done
+            // count the samples per cell; the thread that has a sample finds
+            // its optical thickness
+            int rank_u[kScatterPer];
+            float delta_u[kScatterPer];
+#pragma unroll
+            for (int u = 0; u < kScatterPer; ++u) {
+                if (seg_u[u] < 0) continue;
+                rank_u[u] = atomicAdd(&s_cnt[code_u[u] & (kBrickCells - 1)], 1);
+                delta_u[u] = sample_delta(g, parts.g[seg_u[u]].w, parts.t_far[seg_u[u]], (unsigned)code_u[u] >> 9);
+                s_tau[u * kScatterThreads + t] = fmaxf(val_u[u].x, 0.0f) * delta_u[u];
             }
             __syncthreads();
             {
@@ -1790,58 +1823,79 @@ void seg_scatter_kernel(GridDev g, BinArgs a) {
                 s_coff[t] = (int)block_scan_excl<kScatterThreads>(s_cnt[t], &all);
                 if (t == 0) s_coff[kBrickCells] = (int)all;
             }
-            // the reverse recurrence of each segment over its samples of the pass
-            if (t < ns && occ > 0) {
-                const int e_lo = max(s_pre[t], q0) - q0, e_hi = min(s_pre[t] + occ, q0 + nq) - q0;
-                if (e_lo < e_hi) {
-                    float o[3], d[3];
-                    load_ray_lane(a, sg.x, o, d);
-                    RayGeom r;
-                    const int n = ray_setup(g, o, d, r);
-                    (void)n;
-                    for (int e = e_hi - 1; e >= e_lo; --e) {
-                        LdsSample &sm = s_rec[e];
-                        const int k = (unsigned)sm.seg >> 9;
-                        const float delta = sample_at(g, r, k).delta;
-                        const Q4 v = {sm.v[0], sm.v[1], sm.v[2], sm.v[3]};
-                        const float sd = fmaxf(v.s, 0.0f) * delta;
-                        const double tau_before = fmax(st.tau_after - (double)sd, 0.0);
-                        const float T_before = expf(-(float)tau_before);
-                        const float wk = T_before * (-expm1f(-sd));
-                        const float gc = st.gr[0] * fmaxf(v.r, 0.0f) + st.gr[1] * fmaxf(v.g, 0.0f) +
-                                         st.gr[2] * fmaxf(v.b, 0.0f);
-                        const float cs = CAUCHY ? cauchy_grad(a.pri, v.s, &ls) : 0.0f;
-                        sm.v[0] = v.s > 0.0f ? delta * (st.T_after * gc - st.gR) + cs : 0.0f;
-                        sm.v[1] = v.r > 0.0f ? wk * st.gr[0] : 0.0f;
-                        sm.v[2] = v.g > 0.0f ? wk * st.gr[1] : 0.0f;
-                        sm.v[3] = v.b > 0.0f ? wk * st.gr[2] : 0.0f;
-                        st.gR += wk * gc;
-                        st.tau_after = tau_before;
-                        st.T_after = T_before;
-                    }
+            // the depth before each sample, back along each segment
+            for (int e = e_hi - 1; e >= e_lo; e -= kChainU) {
+                float x[kChainU];
+#pragma unroll
+                for (int u = 0; u < kChainU; ++u) x[u] = s_tau[max(e - u, e_lo)];
+#pragma unroll
+                for (int u = 0; u < kChainU; ++u) {
+                    if (e - u < e_lo) break;
+                    st.tau_after = fmax(st.tau_after - (double)x[u], 0.0);
+                    s_tau[e - u] = (float)st.tau_after;
                 }
             }
             __syncthreads();
-            // sort by cell: each thread takes its samples (now with their
-            // gradients) back, then puts every one in its cell's range
-            LdsSample mine[kScatterPer];
-#pragma unroll
-            for (int u = 0; u < kScatterPer; ++u)
-                if (seg_u[u] >= 0) mine[u] = s_rec[u * kScatterThreads + t];
-            __syncthreads();
+            // each sample's weight and g . colour
+            float em_u[kScatterPer];
 #pragma unroll
             for (int u = 0; u < kScatterPer; ++u) {
-                if (seg_u[u] >= 0) {
-                    mine[u].seg = seg_u[u];
-                    s_rec[s_coff[cell_u[u]] + rank_u[u]] = mine[u];
+                if (seg_u[u] < 0) continue;
+                const int q = u * kScatterThreads + t;
+                const float4 gr = parts.g[seg_u[u]], v = val_u[u];
+                em_u[u] = -expm1f(-(fmaxf(v.x, 0.0f) * delta_u[u]));
+                s_w[q] = expf(-s_tau[q]) * em_u[u];
+                s_gc[q] = gr.x * fmaxf(v.y, 0.0f) + gr.y * fmaxf(v.z, 0.0f) + gr.z * fmaxf(v.w, 0.0f);
+            }
+            __syncthreads();
+            // g . R after each sample, back along each segment
+            for (int e = e_hi - 1; e >= e_lo; e -= kChainU) {
+                float x[kChainU], y[kChainU];
+#pragma unroll
+                for (int u = 0; u < kChainU; ++u) {
+                    x[u] = s_w[max(e - u, e_lo)];
+                    y[u] = s_gc[max(e - u, e_lo)];
+                }
+#pragma unroll
+                for (int u = 0; u < kChainU; ++u) {
+                    if (e - u < e_lo) break;
+                    s_w[e - u] = st.gR;
+                    st.gR += x[u] * y[u];
                 }
             }
+            __syncthreads();
+            LdsSample mine[kScatterPer];
+#pragma unroll
+            for (int u = 0; u < kScatterPer; ++u) {
+                if (seg_u[u] < 0) continue;
+                const int q = u * kScatterThreads + t;
+                const float4 gr = parts.g[seg_u[u]], v = val_u[u], pos = a.srec[slot_of(u)].pos;
+                // the segment's next sample, or the end of its part of the pass
+                const bool last = q + 1 >= nq || q0 + q + 1 >= s_pre[seg_u[u] + 1];
+                const float T_after = expf(-(last ? parts.tau[seg_u[u]] : s_tau[q + 1]));
+                const float wk = expf(-s_tau[q]) * em_u[u];
+                const float cs = CAUCHY ? cauchy_grad(a.pri, v.x, &ls) : 0.0f;
+                mine[u].f[0] = pos.x;
+                mine[u].f[1] = pos.y;
+                mine[u].f[2] = pos.z;
+                mine[u].v[0] = v.x > 0.0f ? delta_u[u] * (T_after * s_gc[q] - s_w[q]) + cs : 0.0f;
+                mine[u].v[1] = v.y > 0.0f ? wk * gr.x : 0.0f;
+                mine[u].v[2] = v.z > 0.0f ? wk * gr.y : 0.0f;
+                mine[u].v[3] = v.w > 0.0f ? wk * gr.z : 0.0f;
+                mine[u].seg = seg_u[u];
+            }
+            __syncthreads();  // the chains' values read
+            // sort by cell: every sample into its cell's range
+#pragma unroll
+            for (int u = 0; u < kScatterPer; ++u)
+                if (seg_u[u] >= 0) s_rec[s_coff[code_u[u] & (kBrickCells - 1)] + rank_u[u]] = mine[u];
             __syncthreads();
 
             // each lane sums its voxels' contributions and flushes them
 #pragma unroll 1
-            for (int rr = 0; rr < kVoxRounds; ++rr) {
-                const int p = t + rr * kScatterThreads;
+            for (int v0 = 0; v0 < n_vox; v0 += kScatterThreads) {
+                const int vi = v0 + t;
+                const int id = vi < n_vox ? s_vid[vi] : -1, p = vi < n_vox ? s_vpos[vi] : 0;
                 float acc[28];
 #pragma unroll
                 for (int v = 0; v < 28; ++v) acc[v] = 0.0f;
@@ -1861,11 +1915,11 @@ void seg_scatter_kernel(GridDev g, BinArgs a) {
                         // the voxel is corner o (x: bit 2) of the cell p - o
                         const int cx = px - ((o >> 2) & 1), cy = py - ((o >> 1) & 1), cz = pz - (o & 1);
                         unsigned ent = 0u;
-                        if (vid[rr] >= 0 && cx >= 0 && cy >= 0 && cz >= 0 && cx < PLX_BRICK && cy < PLX_BRICK &&
+                        if (id >= 0 && cx >= 0 && cy >= 0 && cz >= 0 && cx < PLX_BRICK && cy < PLX_BRICK &&
                             cz < PLX_BRICK) {
                             const int cell = (cx << 6) | (cy << 3) | cz;
-                            const int c0 = s_coff[cell], n = s_coff[cell + 1] - c0;
-                            if (n > 0) ent = (unsigned)c0 | ((unsigned)n << 11) | ((unsigned)o << 22);
+                            const int r0 = s_coff[cell], n = s_coff[cell + 1] - r0;
+                            if (n > 0) ent = (unsigned)r0 | ((unsigned)n << 11) | ((unsigned)o << 22);
                         }
 #pragma unroll
                         for (int j = 0; j < 8; ++j)
@@ -1916,7 +1970,7 @@ void seg_scatter_kernel(GridDev g, BinArgs a) {
                         qr[7] = 0u;
                     }
                 }
-                flush_voxel_rows(stage, acc, any ? vid[rr] : -1, a.grad, a.touched);
+                flush_voxel_rows(stage, acc, any ? id : -1, a.grad, a.touched);
             }
             __syncthreads();
         }
