@@ -1051,8 +1051,11 @@ __global__ __launch_bounds__(kThreads) void seg_fwd_brick_kernel(GridDev g, BinA
 //  2. every lane takes samples of the group (all lanes busy, whatever the
 //     segments' lengths) and interpolates them from the brick's corner
 //     records, staged in LDS (FP32 in two halves along x of 5 x 9 x 9
-//     corners, 45 KB, so that two workgroups fit on a CU; 16-bit records
-//     whole), storing the values in the sample's record;
+//     corners, 45 KB, so that two workgroups fit on a CU, with the samples
+//     listed by half first, as lanes that pass over the other half's samples
+//     idle: 1.84 -> 1.76 ms for 1M rays through 512^3; 16-bit records whole),
+//     storing the values in the sample's record (0.66 ms of that time is the
+//     interpolation: 56 16-byte LDS reads per sample);
 //  3. the lanes of a segment compose runs of its records, each with the
 //     transmittance from the run's start, and chain the runs (a run's colour
 //     times the transmittance of the runs before it).
@@ -1062,7 +1065,8 @@ __global__ __launch_bounds__(kThreads) void seg_fwd_brick_kernel(GridDev g, BinA
 // composition's products differ.
 
 constexpr int kFwdThreads = 512;  // threads of a forward workgroup
-constexpr int kFwdSegs = 512;     // segments per group
+constexpr int kFwdSegs = 384;     // segments per group
+constexpr int kFwdList = 2048;    // samples listed by half at a time (FP32)
 constexpr int kWalkRun = 8;       // consecutive samples a walking lane tests at once
 // Segments per brick (on average over the call) from which the training call
 // takes this forward: with fewer, most of a 512-thread workgroup idles in the
@@ -1080,9 +1084,9 @@ template <int DT> struct FwdStage {
     static constexpr int kPlanes = PLX_BRICK / kHalves + 1;  // corner planes along x per half
     static constexpr int kWords = StagedRec<DT>::kWords;
     static constexpr int kVox = kPlanes * 81;
-    // samples a thread keeps across the halves (FP32: two, within 128 registers)
-    static constexpr int kPer = DT == PLX_F32 ? 2 : 4;
+    static constexpr int kPer = 4;  // samples a thread finds at a time
     static constexpr int kChunk = kPer * kFwdThreads;
+    static_assert(kHalves == 1 || kChunk <= kFwdList, "a chunk's samples fit the list");
 };
 
 // Stages the corner records of planes x = x0 .. x0 + kPlanes - 1 of the
@@ -1158,6 +1162,10 @@ void seg_fwd_samples_kernel(GridDev g, BinArgs a) {
     __shared__ float4 s_y4[kFwdSegs * 3];      // SH basis of each segment's ray (9 of 12 floats)
     __shared__ int s_pre[kFwdSegs + 1];        // first sample of each segment in the group's numbering
     __shared__ int64_t s_soff[kFwdSegs];       // its first sample slot
+    // a chunk's samples (segment << 11 | number in the chunk): those of the
+    // lower half from the front, those of the upper from the back
+    __shared__ uint32_t s_list[FS::kHalves == 2 ? kFwdList : 1];
+    __shared__ int s_nlist[2];
     if (blockIdx.x >= (unsigned)a.n_brick) return;
     const int t = threadIdx.x;
     float *s_y = reinterpret_cast<float *>(s_y4);
@@ -1245,64 +1253,102 @@ void seg_fwd_samples_kernel(GridDev g, BinArgs a) {
         if (t == 0) s_pre[kFwdSegs] = tot;
         __syncthreads();  // positions stored, s_pre / s_soff / s_y / the staging written
 
-        // 2. values: FS::kPer samples per thread per chunk; the chunk takes the
-        // halves starting with the one in LDS
+        // 2. values.  The segment of sample q of the group:
+        auto seg_of = [&](int q) {
+            int lo = 0, hi = ns - 1;  // last segment whose first sample is <= q
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (s_pre[mid] <= q) lo = mid;
+                else hi = mid - 1;
+            }
+            return lo;
+        };
+        // interpolates a sample whose corners are staged from plane x0 on
+        auto evaluate = [&](int seg, const float4 &pos, int x0, SampleRec *rec) {
+            const int code = __float_as_int(pos.w);
+            const int lx = ((code >> 6) & (PLX_BRICK - 1)) - x0, cy = (code >> 3) & (PLX_BRICK - 1),
+                      cz = code & (PLX_BRICK - 1);
+            float y[9];
+#pragma unroll
+            for (int l = 0; l < 9; ++l) y[l] = s_y[seg * 12 + l];
+            const float f[3] = {pos.x, pos.y, pos.z};
+            float w[8];
+            corner_weights(f, w);
+            Q4 v = q4_zero();
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const int p = (lx + ((c >> 2) & 1)) * 81 + (cy + ((c >> 1) & 1)) * 9 + (cz + (c & 1));
+                const Q4 qc = project_staged<DT>(s_rec + p * W, y);
+                v.s += w[c] * qc.s;
+                v.r += w[c] * qc.r;
+                v.g += w[c] * qc.g;
+                v.b += w[c] * qc.b;
+            }
+            rec->val = make_float4(v.s, v.r, v.g, v.b);
+        };
         for (int q0 = 0; q0 < tot; q0 += FS::kChunk) {
             int seg_u[FS::kPer];
-            int64_t slot_u[FS::kPer];
-            float4 pos_u[FS::kPer];
+            SampleRec *rec_u[FS::kPer];
 #pragma unroll
             for (int u = 0; u < FS::kPer; ++u) {
                 const int q = q0 + u * kFwdThreads + t;
                 seg_u[u] = -1;
-                slot_u[u] = 0;
+                rec_u[u] = a.srec;
                 if (q < tot) {
-                    int lo = 0, hi = ns - 1;  // last segment whose first sample is <= q
-                    while (lo < hi) {
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (s_pre[mid] <= q) lo = mid;
-                        else hi = mid - 1;
-                    }
-                    seg_u[u] = lo;
-                    slot_u[u] = s_soff[lo] + (q - s_pre[lo]);
+                    seg_u[u] = seg_of(q);
+                    rec_u[u] = a.srec + s_soff[seg_u[u]] + (q - s_pre[seg_u[u]]);
                 }
             }
+            if constexpr (FS::kHalves == 1) {
+                float4 pos_u[FS::kPer];
 #pragma unroll
-            for (int u = 0; u < FS::kPer; ++u)
-                if (seg_u[u] >= 0) pos_u[u] = a.srec[slot_u[u]].pos;
-            for (int hh = 0; hh < FS::kHalves; ++hh) {
-                const int h = (cur_half + hh) % FS::kHalves;
-                if (h != cur_half) {
-                    __syncthreads();  // the other half's reads are done
-                    stage_planes<DT>(g, s_rec, s_id, h * (FS::kPlanes - 1));
-                    __syncthreads();
-                    cur_half = h;
-                }
+                for (int u = 0; u < FS::kPer; ++u)
+                    if (seg_u[u] >= 0) pos_u[u] = rec_u[u]->pos;
+#pragma unroll
+                for (int u = 0; u < FS::kPer; ++u)
+                    if (seg_u[u] >= 0) evaluate(seg_u[u], pos_u[u], 0, rec_u[u]);
+            } else {
+                // list the chunk's samples by half, so that the lanes that
+                // take a half's are all busy
+                int code_u[FS::kPer];
+#pragma unroll
+                for (int u = 0; u < FS::kPer; ++u)
+                    if (seg_u[u] >= 0) code_u[u] = __float_as_int(rec_u[u]->pos.w);
+                if (q0 > 0) __syncthreads();  // the previous chunk's list and counts read
+                if (t < 2) s_nlist[t] = 0;
+                __syncthreads();
 #pragma unroll
                 for (int u = 0; u < FS::kPer; ++u) {
-                    if (seg_u[u] < 0) continue;
-                    const int code = __float_as_int(pos_u[u].w);
-                    const int cx = (code >> 6) & (PLX_BRICK - 1), cy = (code >> 3) & (PLX_BRICK - 1),
-                              cz = code & (PLX_BRICK - 1);
-                    const int lx = cx - h * (FS::kPlanes - 1);
-                    if (lx < 0 || lx >= FS::kPlanes - 1) continue;  // the sample's cell is in the other half
-                    float y[9];
-#pragma unroll
-                    for (int l = 0; l < 9; ++l) y[l] = s_y[seg_u[u] * 12 + l];
-                    const float f[3] = {pos_u[u].x, pos_u[u].y, pos_u[u].z};
-                    float w[8];
-                    corner_weights(f, w);
-                    Q4 v = q4_zero();
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) {
-                        const int p = (lx + ((c >> 2) & 1)) * 81 + (cy + ((c >> 1) & 1)) * 9 + (cz + (c & 1));
-                        const Q4 qc = project_staged<DT>(s_rec + p * W, y);
-                        v.s += w[c] * qc.s;
-                        v.r += w[c] * qc.r;
-                        v.g += w[c] * qc.g;
-                        v.b += w[c] * qc.b;
+                    const int q = u * kFwdThreads + t;
+                    const bool upper = seg_u[u] >= 0 && ((code_u[u] >> 6) & (PLX_BRICK - 1)) >= FS::kPlanes - 1;
+                    const uint64_t m1 = __ballot(upper), m0 = __ballot(seg_u[u] >= 0 && !upper);
+                    int at0 = 0, at1 = 0;
+                    if (lane_id() == 0) {
+                        if (m0) at0 = atomicAdd(&s_nlist[0], __popcll(m0));
+                        if (m1) at1 = atomicAdd(&s_nlist[1], __popcll(m1));
                     }
-                    a.srec[slot_u[u]].val = make_float4(v.s, v.r, v.g, v.b);
+                    at0 = __shfl(at0, 0) + lanes_below(m0);
+                    at1 = kFwdList - 1 - __shfl(at1, 0) - lanes_below(m1);
+                    if (seg_u[u] >= 0) s_list[upper ? at1 : at0] = (uint32_t)seg_u[u] << 11 | (uint32_t)q;
+                }
+                __syncthreads();
+                for (int hh = 0; hh < FS::kHalves; ++hh) {
+                    const int h = hh == 0 ? cur_half : 1 - cur_half;
+                    const int n_h = s_nlist[h];
+                    if (hh == 1) {
+                        if (n_h == 0) break;  // the same in every thread
+                        __syncthreads();      // the other half's reads are done
+                        stage_planes<DT>(g, s_rec, s_id, h * (FS::kPlanes - 1));
+                        __syncthreads();
+                        cur_half = h;
+                    }
+                    for (int e = t; e < n_h; e += kFwdThreads) {
+                        const uint32_t ent = s_list[h ? kFwdList - 1 - e : e];
+                        const int seg = (int)(ent >> 11);
+                        SampleRec *rec = a.srec + s_soff[seg] + (q0 + (int)(ent & 2047u) - s_pre[seg]);
+                        evaluate(seg, rec->pos, h * (FS::kPlanes - 1), rec);
+                    }
+                    if (hh == 1) break;
                 }
             }
         }
