@@ -551,12 +551,18 @@ def ray_order(g: PlxGrid, n_rays: int) -> bool:
 def ray_order_grad(g: PlxGrid, n_rays: int) -> bool:
     """As ray_order, for a separate forward and backward pass, where lists
     also cost a forward of their own: ray order while few rays cross a brick
-    (n_rays times the bricks along a ray over all bricks).  5000 rays on 64^3
-    (78) 164 / 277 us, 20,000 (312) 435 / 368; 65,536 on 256^3 (64) 530 / 1300
-    (FP16); 100,000 on 512^3 (24) 1143 / 1797; 16,384 inside a dense 128^3 (64)
-    1646 / 1440; 49,152 through a dense 256x256x128 (77) 4129 / 3302."""
+    (x = n_rays times the bricks along a ray over all bricks), and for small
+    batches, whose lists are mostly fixed costs.  Ray order / lists in us:
+    5000 rays on 64^3 164 / 277; sparse grids (up to a quarter occupied):
+    300,000 on 512^3 at 5% (x = 73) 2603 / 4004 (BF16), 230,400 on 380^3 at 4%
+    (100) 1342 / 1723 and at 10% 2966 / 3124 (at x = 130 3717 / 3439), 64,000 on
+    128^3 at 12% (250) 447 / 617; dense grids: 128^3 from outside (75) 907 /
+    1197, but 16,384 from inside it (64) 1646 / 1440 and 49,152 through a
+    256x256x128 (77) 4129 / 3302."""
     b = [-(-(int(r) - 1) // 8) for r in g.reso]
-    return n_rays < 8192 or n_rays * sum(b) < 3 * 72 * b[0] * b[1] * b[2]
+    sparse = 4 * int(g.n_vox) < int(g.reso[0]) * int(g.reso[1]) * int(g.reso[2])
+    return (n_rays < (65536 if sparse else 8192)
+            or n_rays * sum(b) < 3 * (100 if sparse else 50) * b[0] * b[1] * b[2])
 
 
 class RayWork:
