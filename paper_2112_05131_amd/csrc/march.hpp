@@ -80,34 +80,27 @@ __device__ __forceinline__ int64_t brick_id(const GridDev &g, const int b[3]) {
     return ((int64_t)b[0] * g.by + b[1]) * g.bz + b[2];
 }
 
-// Number of further samples after sample k (in the direction of travel)
-// that certainly stay inside the box of bricks within R of brick b, where
-// sample k lies (at t = t_near + k*step): the box's exit parameter along the
-// ray, less a margin of 5% of a step.
-// Both walks over a ray's bricks (counting and emitting its segments) must
-// cut identical segments, so this runs without FMA contraction like the
-// sample recipe itself.
-template <bool FORWARD>
-__device__ __forceinline__ int samples_in_box(const GridDev &g, const RayGeom &r, int k,
-                                              const int b[3], int R) {
+// Number of samples before sample k (at t = t_near + k*step), back along the
+// ray, that certainly stay inside the box of bricks within R of brick b, where
+// sample k lies: the box's entry parameter along the ray, less a margin of 5%
+// of a step.
+__device__ __forceinline__ int samples_behind(const GridDev &g, const RayGeom &r, int k, const int b[3], int R) {
 #pragma clang fp contract(off)
     const int nb[3] = {g.bx, g.by, g.bz};
     const float t = r.t_near + (float)k * g.step;
-    float t_edge = FORWARD ? __builtin_inff() : -__builtin_inff();
+    float t_edge = -__builtin_inff();
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const float dg = r.dg[a];
         if (dg == 0.0f) continue;
         // box faces on the grid boundary are never crossed by a sample
-        const bool up = (dg > 0.0f) == FORWARD;
+        const bool up = dg < 0.0f;
         const int bf = up ? b[a] + R : b[a] - R;
         if (up ? bf >= nb[a] - 1 : bf <= 0) continue;
         const float face = (float)((up ? bf + 1 : bf) * PLX_BRICK);
-        const float tf = (face - r.og[a]) / dg;
-        t_edge = FORWARD ? fminf(t_edge, tf) : fmaxf(t_edge, tf);
+        t_edge = fmaxf(t_edge, (face - r.og[a]) / dg);
     }
-    const float span = FORWARD ? (t_edge - t) : (t - t_edge);
-    float q = span / g.step - kSkipMargin;
+    float q = (t - t_edge) / g.step - kSkipMargin;
     q = q < (float)kMaxSamples ? q : (float)kMaxSamples;
     return q > 0.0f ? (int)q : 0;
 }
@@ -213,8 +206,8 @@ __device__ __forceinline__ RaySkip ray_skip(const GridDev &g, const RayGeom &r) 
     return s;
 }
 
-// samples_in_box<true> with products by reciprocals for the quotients, for
-// walks that test every sample they do not skip: the margin also covers the
+// Number of further samples after sample k, as samples_behind before it, with
+// products by reciprocals for the quotients: the margin also covers the
 // rounding of the exit parameter (a few ulps of t_edge, in steps).
 __device__ __forceinline__ int skip_box(const GridDev &g, const RayGeom &r, const RaySkip &q, int k,
                                         const int b[3], int R) {

@@ -388,7 +388,7 @@ __device__ __forceinline__ void backward_ray(const GridDev &g, const RayArgs &a,
                     const Sample s_hi = sample_at(g, r, k_hi);
                     const int b[3] = {s_hi.cell[0] >> 3, s_hi.cell[1] >> 3, s_hi.cell[2] >> 3};
                     const int D = g.bdist[brick_id(g, b)];
-                    if (D > 0) step = max(step, samples_in_box<false>(g, r, k_hi, b, D - 1) + 1);
+                    if (D > 0) step = max(step, samples_behind(g, r, k_hi, b, D - 1) + 1);
                 }
                 k_hi -= step;
             }

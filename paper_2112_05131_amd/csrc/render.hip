@@ -1,10 +1,12 @@
 // render.hip -- differentiable volume rendering over the sparse voxel grid
 // (Sec. 3.1-3.3, Eq. (1); supplement B.1) for gfx950.
 //
-// Work mapping: one ray per lane, 256 rays per block.  A heavily sampled
-// ray is a long chain of dependent memory accesses (occupancy bits, index
-// entries, voxel records), so the kernels keep as many rays in flight as the
-// register file allows rather than spreading one ray over a wave.
+// Work mapping: two orders of the same work.  In ray order several lanes march
+// a ray (march.hpp): the views here, and the batches of ray_order.hip.  In
+// brick order, for large batches, a ray is cut into segments, one per occupied
+// brick of 8^3 cells, and the segments are sorted by brick: a lane, or a
+// workgroup per brick, takes them, so that rays crossing the same voxels share
+// their records and send their gradients as one.
 //
 // SH factorisation.  The SH basis depends only on the ray direction, so the
 // pre-activation colour of a sample is sum_c w_c (sum_l y_l k_{c,l}): when a
@@ -514,52 +516,81 @@ __device__ int64_t block_scan_excl(int64_t v, int64_t *total) {
     return before + x - v;
 }
 
-// The counts are c[0], c[stride], c[2*stride], ... (stride 2 reads one half
-// of an array of 64-bit counter pairs).
-__global__ __launch_bounds__(kScanT) void count_sum_kernel(const unsigned *c, int64_t n, int stride,
-                                                           int64_t *bsum) {
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanI;
+// Up to three arrays of counts scanned by the same three launches (one array
+// each took nine, about 5 us apiece whatever the batch).  The counts of an
+// array are c[0], c[stride], c[2*stride], ... (stride 2 reads one half of an
+// array of 64-bit counter pairs).
+struct ScanOf {
+    const unsigned *c;
+    int64_t n, nb;       // counts, and blocks of them
+    int stride;
+    int64_t *bsum, *boff;  // [nb], [nb + 1]
+    int64_t *out;        // [n + 1]: out[i] = sum of c[0..i)
+    int64_t *total;      // optional second copy of out[n]
+};
+struct ScanArgs {
+    ScanOf of[3];
+    int n_of;
+};
+
+// The array of a block (nb[0] blocks of the first, then those of the second
+// ...); *blk gets its number there.
+__device__ __forceinline__ const ScanOf &scan_of(const ScanArgs &a, int64_t *blk) {
+    int64_t b = blockIdx.x;
+    int k = 0;
+    while (k + 1 < a.n_of && b >= a.of[k].nb) b -= a.of[k++].nb;
+    *blk = b;
+    return a.of[k];
+}
+
+__global__ __launch_bounds__(kScanT) void count_sum_kernel(ScanArgs a) {
+    int64_t blk;
+    const ScanOf &q = scan_of(a, &blk);
+    const int64_t base = blk * kScanTile + (int64_t)threadIdx.x * kScanI;
     int64_t s = 0;
 #pragma unroll
     for (int i = 0; i < kScanI; ++i)
-        if (base + i < n) s += c[(base + i) * stride];
+        if (base + i < q.n) s += q.c[(base + i) * q.stride];
     int64_t tot;
     block_scan_excl(s, &tot);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+    if (threadIdx.x == 0) q.bsum[blk] = tot;
 }
 
-__global__ __launch_bounds__(kScanT) void block_offsets_kernel(const int64_t *bsum, int64_t nb,
-                                                               int64_t *boff) {
+// One block per array.
+__global__ __launch_bounds__(kScanT) void block_offsets_kernel(ScanArgs a) {
+    const ScanOf &q = a.of[blockIdx.x];
     int64_t carry = 0;
-    for (int64_t b0 = 0; b0 < nb; b0 += kScanT) {
+    for (int64_t b0 = 0; b0 < q.nb; b0 += kScanT) {
         const int64_t b = b0 + threadIdx.x;
         int64_t tot;
-        const int64_t ex = block_scan_excl(b < nb ? bsum[b] : 0, &tot);
-        if (b < nb) boff[b] = carry + ex;
+        const int64_t ex = block_scan_excl(b < q.nb ? q.bsum[b] : 0, &tot);
+        if (b < q.nb) q.boff[b] = carry + ex;
         carry += tot;
     }
-    if (threadIdx.x == 0) boff[nb] = carry;
+    if (threadIdx.x == 0) {
+        q.out[q.n] = carry;
+        if (q.total) *q.total = carry;
+    }
 }
 
-// out[i] = sum of c[0..i), out[n] = total.
-__global__ __launch_bounds__(kScanT) void count_scan_kernel(const unsigned *c, int64_t n, int stride,
-                                                            const int64_t *boff, int64_t *out) {
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanI;
+__global__ __launch_bounds__(kScanT) void count_scan_kernel(ScanArgs a) {
+    int64_t blk;
+    const ScanOf &q = scan_of(a, &blk);
+    const int64_t base = blk * kScanTile + (int64_t)threadIdx.x * kScanI;
     unsigned v[kScanI];
     int64_t s = 0;
 #pragma unroll
     for (int i = 0; i < kScanI; ++i) {
-        v[i] = base + i < n ? c[(base + i) * stride] : 0u;
+        v[i] = base + i < q.n ? q.c[(base + i) * q.stride] : 0u;
         s += v[i];
     }
     int64_t tot;
-    int64_t r = boff[blockIdx.x] + block_scan_excl(s, &tot);
+    int64_t r = q.boff[blk] + block_scan_excl(s, &tot);
 #pragma unroll
     for (int i = 0; i < kScanI; ++i) {
-        if (base + i < n) out[base + i] = r;
+        if (base + i < q.n) q.out[base + i] = r;
         r += v[i];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = boff[gridDim.x];
 }
 
 __global__ void zero_u32_kernel(unsigned *p, int64_t n) {
@@ -615,6 +646,7 @@ struct BinArgs {
     int64_t *bsoff;      // [n_bins + 1] first sample slot of each bin
     unsigned *blist;     // [n_brick] binning-order positions of the bricks with segments
     unsigned *nbrick;    // device count of blist entries
+    int64_t *totals;     // [2] segments and sample slots (after nbrick)
     int64_t n_brick;
     int64_t *soff;       // [n_seg] bin-major: first sample slot of each segment
     int *nocc;           // [n_seg] bin-major: occupied samples the replay recorded
@@ -647,67 +679,118 @@ __device__ __forceinline__ void load_ray_lane(const BinArgs &a, int64_t ray, flo
 }
 
 // Calls f(brick order position, first sample, last sample) for every brick
-// with an occupied cell that the ray's samples enter, in ray order; boxes of
-// empty bricks are skipped with the distance field, and inside a brick only
-// the samples near its exit face are placed.
+// with an occupied cell that the ray's samples enter with a first sample in
+// [ks, ke), in ray order; boxes of empty bricks are skipped with the distance
+// field, and inside a brick only the samples near its exit face are placed.
+// A segment is a maximal run of the ray's samples in one occupied brick, so
+// the parts of a ray, walked apart, give the segments of the whole.
 template <class F>
-__device__ __forceinline__ void walk_bricks(const GridDev &g, const RayGeom &r, int n, F &&f) {
-    int k = 0;
-    while (k < n) {
+__device__ __forceinline__ void walk_bricks(const GridDev &g, const RayGeom &r, int n, int ks, int ke, F &&f) {
+    const RaySkip rs = ray_skip(g, r);
+    int k = ks;
+    // a brick that the part begins in the middle of belongs to the part before
+    bool inside = false;
+    if (k > 0 && k < ke) {
+        const Sample s0 = sample_at(g, r, k - 1), s1 = sample_at(g, r, k);
+        inside = s0.cell[0] / PLX_BRICK == s1.cell[0] / PLX_BRICK && s0.cell[1] / PLX_BRICK == s1.cell[1] / PLX_BRICK &&
+                 s0.cell[2] / PLX_BRICK == s1.cell[2] / PLX_BRICK;
+    }
+    while (k < ke) {
         const Sample s = sample_at(g, r, k);
         const int b[3] = {s.cell[0] / PLX_BRICK, s.cell[1] / PLX_BRICK, s.cell[2] / PLX_BRICK};
         const int64_t bid = brick_id(g, b);
         const int D = g.bdist[bid];
-        const int m = samples_in_box<true>(g, r, k, b, D > 0 ? D - 1 : 0);
+        const int m = skip_box(g, r, rs, k, b, D > 0 ? D - 1 : 0);
         if (D > 0) {
             k += m + 1;
+            inside = false;
             continue;
         }
-        int ke = m < n - 1 - k ? k + m : n - 1;
-        while (ke + 1 < n) {
-            const Sample s2 = sample_at(g, r, ke + 1);
+        int kl = m < n - 1 - k ? k + m : n - 1;
+        while (kl + 1 < n) {
+            const Sample s2 = sample_at(g, r, kl + 1);
             if (s2.cell[0] / PLX_BRICK != b[0] || s2.cell[1] / PLX_BRICK != b[1] ||
                 s2.cell[2] / PLX_BRICK != b[2])
                 break;
-            ++ke;
+            ++kl;
         }
-        f(brick_order(g, b), k, ke);
-        k = ke + 1;
+        if (!inside) f(brick_order(g, b), k, kl);
+        inside = false;
+        k = kl + 1;
     }
 }
 
+// Lanes that walk a ray, each an eighth of its samples: a walk is a chain of
+// distance reads, which a lane per ray leaves bare with few rays.  Count and
+// emit in us: 5,000 rays inside 128^3 58 + 81, now 16 + 19; 20,011 through
+// 256x256x128 42 + 57, now 25 + 30.  1M rays on 256^3 would still gain (180 +
+// 191 with a lane per ray, 160 + 179 with eight), but a batch that large is
+// binned beside the step before it, whose kernels the eightfold threads slow
+// (two steps of 1M rays on 512^3 10.28 ms, with eight lanes 10.44).
+// The lanes' segment counts, 16 bits each, wait for the emit walk in the ray's
+// dL/dC, which the render calls write later; a part has no more segments than
+// a line crosses bricks.
+constexpr int kWalkParts = 8;
+constexpr int64_t kWalkPartRays = 1 << 17;
+inline int walk_parts(const GridDev &g, int64_t n_rays) {
+    return n_rays <= kWalkPartRays && (int64_t)g.bx + g.by + g.bz < (1 << 16) ? kWalkParts : 1;
+}
+
+template <int PARTS>
 __global__ __launch_bounds__(kThreads) void seg_count_kernel(GridDev g, BinArgs a) {
     const int blk = xcd_logical_block(blockIdx.x, a.nb8);
     if (blk >= a.n_blocks) return;
-    const int64_t ray = (int64_t)blk * kThreads + threadIdx.x;
+    const int64_t t = (int64_t)blk * kThreads + threadIdx.x, ray = t / PARTS;
     if (ray >= a.n_rays) return;
+    const int part = (int)(t % PARTS);
     float o[3], d[3];
     load_ray_lane(a, ray, o, d);
     RayGeom r;
     const int n = ray_setup(g, o, d, r);
     unsigned cnt = 0;
-    walk_bricks(g, r, n, [&](int64_t bid, int k0, int k1) {
-        ++cnt;
-        const int64_t bin = seg_bin(bid, k0, k1);
-        if (a.bcnt64) atomicAdd(a.bcnt64 + bin, 1ull | ((unsigned long long)(k1 - k0 + 1) << 32));
-        else atomicAdd(a.bcount + bin, 1u);
-    });
-    a.nseg[ray] = cnt;
+    walk_bricks(g, r, n, (int)((int64_t)n * part / PARTS), (int)((int64_t)n * (part + 1) / PARTS),
+                [&](int64_t bid, int k0, int k1) {
+                    ++cnt;
+                    const int64_t bin = seg_bin(bid, k0, k1);
+                    if (a.bcnt64) atomicAdd(a.bcnt64 + bin, 1ull | ((unsigned long long)(k1 - k0 + 1) << 32));
+                    else atomicAdd(a.bcount + bin, 1u);
+                });
+    if (PARTS > 1) {
+        reinterpret_cast<uint16_t *>(a.g_ray + ray)[part] = (uint16_t)cnt;
+#pragma unroll
+        for (int m = 1; m < PARTS; m <<= 1) cnt += __shfl_xor(cnt, m, PARTS);
+    }
+    if (part == 0) a.nseg[ray] = cnt;
 }
 
+template <int PARTS>
 __global__ __launch_bounds__(kThreads) void seg_emit_kernel(GridDev g, BinArgs a) {
     const int blk = xcd_logical_block(blockIdx.x, a.nb8);
     if (blk >= a.n_blocks) return;
-    const int64_t ray = (int64_t)blk * kThreads + threadIdx.x;
+    const int64_t t = (int64_t)blk * kThreads + threadIdx.x, ray = t / PARTS;
     if (ray >= a.n_rays) return;
+    const int part = (int)(t % PARTS);
     float o[3], d[3];
     load_ray_lane(a, ray, o, d);
     RayGeom r;
     const int n = ray_setup(g, o, d, r);
     int64_t slot = a.seg_off[ray];
-    const int64_t slot_end = a.seg_off[ray + 1];
+    int64_t slot_end = a.seg_off[ray + 1];
     bool bad = false;
-    walk_bricks(g, r, n, [&](int64_t bid, int k0, int k1) {
+    if (PARTS > 1) {
+        const int own = reinterpret_cast<const uint16_t *>(a.g_ray + ray)[part];
+        int incl = own;
+#pragma unroll
+        for (int m = 1; m < PARTS; m <<= 1) {
+            const int y = __shfl_up(incl, m, PARTS);
+            if (part >= m) incl += y;
+        }
+        bad = slot + __shfl(incl, PARTS - 1, PARTS) != slot_end;
+        slot += incl - own;
+        slot_end = min(slot_end, slot + own);
+    }
+    walk_bricks(g, r, n, (int)((int64_t)n * part / PARTS), (int)((int64_t)n * (part + 1) / PARTS),
+                [&](int64_t bid, int k0, int k1) {
         const int64_t bin = seg_bin(bid, k0, k1);
         const unsigned len = (unsigned)(k1 - k0 + 1);
         // one cursor update gives the segment's position and (with a sample
@@ -2341,19 +2424,25 @@ __global__ void stats_kernel(GridDev g, const float *rays_o, const float *rays_d
     }
 }
 
-// Exclusive scan of n counts into out[0..n] (out[n] = total).  tmp: 2*nb+1
-// int64 where nb = ceil(n / kScanTile).
-int scan_counts(const unsigned *c, int64_t n, int64_t *out, int64_t *tmp, hipStream_t s,
-                const char *fn, int stride = 1) {
+// Adds the exclusive scan of n counts into out[0..n] (out[n] = total) to a.
+// tmp: 2*nb+1 int64 where nb = ceil(n / kScanTile).
+int add_scan(ScanArgs &a, const unsigned *c, int64_t n, int stride, int64_t *out, int64_t *tmp, int64_t *total,
+             const char *fn) {
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
-    if (nb < 1 || nb > 0x7fffffff) return fail(PLX_EINVAL, "%s: bad scan size", fn);
-    int64_t *bsum = tmp, *boff = tmp + nb;
-    count_sum_kernel<<<(unsigned)nb, kScanT, 0, s>>>(c, n, stride, bsum);
+    if (nb < 1 || nb > 0x1fffffff) return fail(PLX_EINVAL, "%s: bad scan size", fn);
+    a.of[a.n_of++] = {c, n, nb, stride, tmp, tmp + nb, out, total};
+    return PLX_OK;
+}
+
+int run_scans(const ScanArgs &a, hipStream_t s, const char *fn) {
+    int64_t nb = 0;
+    for (int k = 0; k < a.n_of; ++k) nb += a.of[k].nb;
+    count_sum_kernel<<<(unsigned)nb, kScanT, 0, s>>>(a);
     int rc = check_launch(fn);
     if (rc) return rc;
-    block_offsets_kernel<<<1, kScanT, 0, s>>>(bsum, nb, boff);
+    block_offsets_kernel<<<(unsigned)a.n_of, kScanT, 0, s>>>(a);
     if ((rc = check_launch(fn))) return rc;
-    count_scan_kernel<<<(unsigned)nb, kScanT, 0, s>>>(c, n, stride, boff, out);
+    count_scan_kernel<<<(unsigned)nb, kScanT, 0, s>>>(a);
     return check_launch(fn);
 }
 
@@ -2404,6 +2493,8 @@ RayBufLayout ray_buf_layout(int64_t n_rays, int64_t nbk, bool samples = true) {
         l.bsoff = off; off += align256((nbk + 1) * 8);
         l.blist = off; off += align256(nbk / kLenClasses * 4);
     }
+    // (the segment and the sample offsets of the bins are scanned together;
+    // the second has its temporaries in the list of bricks, made afterwards)
     l.scan = off; off += align256((scan_tmp_words(n_rays) + scan_tmp_words(nbk)) * 8);
     l.bytes = off;
     return l;
@@ -2458,6 +2549,7 @@ void attach_ray_buf(BinArgs &a, void *ray_buf, const RayBufLayout &l) {
         a.bcur64 = reinterpret_cast<unsigned long long *>(base + l.bcursor);
         a.bcount = reinterpret_cast<unsigned *>(base + l.bcount);  // the low halves, read at stride 2
         a.nbrick = reinterpret_cast<unsigned *>(base + l.nbrick);
+        a.totals = reinterpret_cast<int64_t *>(base + l.nbrick + 4);
         a.bsoff = reinterpret_cast<int64_t *>(base + l.bsoff);
         a.blist = reinterpret_cast<unsigned *>(base + l.blist);
     } else {
@@ -2527,6 +2619,21 @@ int attach_bins(const plx_grid *grid, const plx_bins *bins, int64_t n_rays, BinA
     return PLX_OK;
 }
 
+// Blocks of the count and emit walks of a's rays; returns the lanes per ray.
+int walk_blocks(const GridDev &g, BinArgs &a) {
+    const int parts = walk_parts(g, a.n_rays);
+    const int64_t nbr = (a.n_rays * parts + kThreads - 1) / kThreads;
+    a.n_blocks = (int)nbr;
+    a.nb8 = round_up8(nbr);
+    return parts;
+}
+
+int emit_launch(const GridDev &g, BinArgs &a, hipStream_t s, const char *fn) {
+    if (walk_blocks(g, a) == 1) seg_emit_kernel<1><<<a.nb8, kThreads, 0, s>>>(g, a);
+    else seg_emit_kernel<kWalkParts><<<a.nb8, kThreads, 0, s>>>(g, a);
+    return check_launch(fn);
+}
+
 // Counting phase: per-ray and per-bin segment counts and their scans.
 // Leaves the total at seg_off[n_rays] on the device.
 int bin_count_launch(const GridDev &g, BinArgs &a, int64_t nbk, int64_t *scan_tmp, hipStream_t s,
@@ -2538,17 +2645,21 @@ int bin_count_launch(const GridDev &g, BinArgs &a, int64_t nbk, int64_t *scan_tm
         a.bcnt64 ? reinterpret_cast<unsigned *>(a.bcnt64) : a.bcount, nz);
     int rc = check_launch(fn);
     if (rc) return rc;
-    const int64_t nbr = (n_rays + kThreads - 1) / kThreads;
-    a.n_blocks = (int)nbr;
-    a.nb8 = round_up8(nbr);
-    seg_count_kernel<<<a.nb8, kThreads, 0, s>>>(g, a);
+    const int parts = walk_blocks(g, a);
+    if (parts == 1) seg_count_kernel<1><<<a.nb8, kThreads, 0, s>>>(g, a);
+    else seg_count_kernel<kWalkParts><<<a.nb8, kThreads, 0, s>>>(g, a);
     if ((rc = check_launch(fn))) return rc;
-    if ((rc = scan_counts(a.nseg, n_rays, a.seg_off, scan_tmp, s, fn))) return rc;
+    ScanArgs q = {};
     int64_t *bin_tmp = scan_tmp + scan_tmp_words(n_rays);
-    if (!a.bcnt64) return scan_counts(a.bcount, nbk, a.boff, bin_tmp, s, fn);
+    if ((rc = add_scan(q, a.nseg, n_rays, 1, a.seg_off, scan_tmp, a.bcnt64 ? a.totals : nullptr, fn))) return rc;
+    if (!a.bcnt64) {
+        if ((rc = add_scan(q, a.bcount, nbk, 1, a.boff, bin_tmp, nullptr, fn))) return rc;
+        return run_scans(q, s, fn);
+    }
     const unsigned *halves = reinterpret_cast<const unsigned *>(a.bcnt64);
-    if ((rc = scan_counts(halves, nbk, a.boff, bin_tmp, s, fn, 2))) return rc;
-    if ((rc = scan_counts(halves + 1, nbk, a.bsoff, bin_tmp, s, fn, 2))) return rc;
+    if ((rc = add_scan(q, halves, nbk, 2, a.boff, bin_tmp, nullptr, fn))) return rc;
+    if ((rc = add_scan(q, halves + 1, nbk, 2, a.bsoff, reinterpret_cast<int64_t *>(a.blist), a.totals + 1, fn))) return rc;
+    if ((rc = run_scans(q, s, fn))) return rc;
     const int64_t n_bricks = nbk / kLenClasses;
     brick_list_kernel<<<(unsigned)((n_bricks + kThreads - 1) / kThreads), kThreads, 0, s>>>(a, n_bricks);
     return check_launch(fn);
@@ -2713,12 +2824,16 @@ int plx_bins_count(const plx_grid *grid, const float *rays_o, const float *rays_
     attach_ray_buf(a, ray_buf, l);
     int64_t *scan_tmp = reinterpret_cast<int64_t *>(static_cast<char *>(ray_buf) + l.scan);
     if ((rc = bin_count_launch(g, a, nbk, scan_tmp, s, fn))) return rc;
-    int64_t total = 0, samples = 0;
-    unsigned bricks = 0;
-    PLX_CHECK_HIP(hipMemcpyAsync(&total, a.seg_off + n_rays, sizeof(total), hipMemcpyDeviceToHost, s), fn);
-    PLX_CHECK_HIP(hipMemcpyAsync(&samples, a.bsoff + nbk, sizeof(samples), hipMemcpyDeviceToHost, s), fn);
-    PLX_CHECK_HIP(hipMemcpyAsync(&bricks, a.nbrick, sizeof(bricks), hipMemcpyDeviceToHost, s), fn);
+    // the status word, the brick count and the two totals lie side by side
+    struct {
+        unsigned status, bricks;
+        int64_t total, samples;
+    } h = {};
+    static_assert(sizeof(h) == 24, "as in the ray buffer");
+    PLX_CHECK_HIP(hipMemcpyAsync(&h, a.status, sizeof(h), hipMemcpyDeviceToHost, s), fn);
     PLX_CHECK_HIP(hipStreamSynchronize(s), fn);
+    const int64_t total = h.total, samples = h.samples;
+    const unsigned bricks = h.bricks;
     if (total < 0 || total > kMaxRaysBinned)
         return fail(PLX_EINVAL, "%s: %lld ray segments, more than one call handles", fn, (long long)total);
     if (samples < 0 || samples > kMaxSampBinned)
@@ -2742,11 +2857,7 @@ int plx_bins_apply(const plx_grid *grid, const float *rays_o, const float *rays_
     a.rays_o = rays_o;
     a.rays_d = rays_d;
     a.n_rays = bins->n_rays;
-    const int64_t nbr = (a.n_rays + kThreads - 1) / kThreads;
-    a.n_blocks = (int)nbr;
-    a.nb8 = round_up8(nbr);
-    seg_emit_kernel<<<a.nb8, kThreads, 0, as_stream(stream)>>>(to_dev(grid), a);
-    return check_launch(fn);
+    return emit_launch(to_dev(grid), a, as_stream(stream), fn);
 }
 
 int plx_bins_verify(const plx_grid *grid, const plx_bins *bins, plx_stream stream) {
@@ -2910,8 +3021,7 @@ int plx_render_train_static(const plx_grid *grid, const plx_render_opts *opts, c
     a.n_seg = cap;  // launch bound; the kernels read the count itself
     a.seg_cap = cap;
     a.n_seg_dev = a.seg_off + n_rays;
-    seg_emit_kernel<<<a.nb8, kThreads, 0, s>>>(g, a);
-    if ((rc = check_launch(fn))) return rc;
+    if ((rc = emit_launch(g, a, s, fn))) return rc;
     a.events = opts->kernel_events;
     a.target = target;
     a.rgb_out = rgb_out;
