@@ -1717,12 +1717,12 @@ void seg_bwd_kernel(GridDev g, BinArgs a) {
 //     slots of the sample buffer;
 //  2. seg_combine forms the per-ray and per-segment quantities as before;
 //  3. seg_scatter (one workgroup per brick with segments) loads the brick's
-//     samples into LDS, runs each segment's reverse recurrence over them
-//     (one lane per segment: transmittance from the FP64 optical depth after
-//     the segment, the radiance collected after it, the sample's gradients
-//     with respect to its density and projected colour), sorts the samples
-//     by cell, and then each lane owns one of the brick's 9^3 corner voxels
-//     and sums the contributions of the samples of the (up to) 8 cells around
+//     samples, forms their gradients with respect to density and projected
+//     colour (the lane that has a sample finds its weight and gradients; one
+//     lane per segment runs the reverse recurrence's two chains, the FP64
+//     optical depth before each sample and the radiance after it), sorts
+//     them in LDS by cell, and then each lane owns one of the brick's stored
+//     corner voxels and sums the contributions of the samples of the (up to) 8 cells around
 //     it, so every voxel gets one 128-B line of atomics per brick instead of
 //     one per segment, and no corner record is read a second time.
 // The terms are those of seg_bwd (Sec. 3.3, Eq. (1) and the chain rule
@@ -1735,7 +1735,8 @@ void seg_bwd_kernel(GridDev g, BinArgs a) {
 // found by the lane that has the sample, and a segment's lane only subtracts
 // depths and sums g . R -- and only the brick's stored voxels are given
 // lanes, in one round where a brick of mostly empty corners took two.
-// 2.24 -> 2.07 ms; about 1.07 are its 21M 64-byte atomic requests (20 G/s).
+// 2.24 -> 2.07 ms; its 21M 64-byte atomic requests, which overlap the rest, would
+// take 1.07 alone (20 G/s).
 
 constexpr int kScatterThreads = 512;       // threads of a scatter workgroup
 constexpr int kScatterSegs = 256;          // segments per pass
