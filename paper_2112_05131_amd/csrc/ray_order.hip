@@ -450,13 +450,17 @@ __global__ __launch_bounds__(256) void rays_prior_kernel(const RayVals *vals, in
     }
 }
 
-// Rays from which 16 lanes per ray (4 rays per wave) fill the chip; below, each
-// ray gets a wave.  Forward without record, 64 / 16 lanes (us): 5000 rays on
-// 64^3 37 / 93, on 256^3 61 / 151; 65,536 rays on 256^3 192 / 232 FP32, 156 /
-// 142 FP16; 640,000 (an 800x800 image of 512^3) 1532 / 968 FP32, 1228 / 594
-// FP16.  Fewer lanes only lose (8 and 4 on that image: 1019 and 1308 FP32):
-// the rays of a list do not form square tiles.
-constexpr int64_t kWaveRays = 16384;
+// Rays from which 16 lanes per ray (4 rays per wave) are the better cut; below,
+// each ray gets a wave.  Forward without record, 64 / 16 lanes (us), FP32:
+// 5000 rays on 64^3 37 / 93, on 256^3 52 / 151; 65,536 rays on 128^3 143 / 152,
+// on 256^3 176 / 231, on 512^3 233 / 366; 131,072 on 128^3 263 / 216, on 256^3
+// 320 / 333, dense 64^3 432 / 407; 640,000 (an 800x800 image of 512^3)
+// 1532 / 968.  16-bit records, which take half the lanes and loads: 32,768
+// rays on 128^3 74 / 72, on 256^3 96 / 109, on 512^3 113 / 151; 65,536 on 128^3
+// 128 / 101, on 256^3 158 / 143, on 512^3 192 / 195.  Fewer lanes only lose (8
+// and 4 on that image: 1019 and 1308 FP32): the rays of a list do not form
+// square tiles.
+template <int DT> constexpr int64_t kWaveRays = DT == PLX_F32 ? 3 << 15 : 3 << 14;
 // Workgroups of a launch; with more rays they stride (a grid holds fewer than
 // 2^32 threads).
 constexpr int64_t kMaxBlocks = 1 << 25;
@@ -464,13 +468,15 @@ constexpr int64_t kMaxBlocks = 1 << 25;
 template <int MODE, bool REC>
 int launch_fwd(const plx_grid *grid, const RayArgs &a, hipStream_t s, const char *fn) {
     const GridDev g = to_dev(grid);
-    if (a.n_rays < kWaveRays) {
-        const unsigned nb = (unsigned)a.n_rays;
-        PLX_DISPATCH_DT(grid->sh_dtype, DT, rays_fwd_kernel<DT, 64, 1, MODE, REC><<<nb, kWave, 0, s>>>(g, a));
-    } else {
-        const unsigned nb = (unsigned)std::min((a.n_rays + 3) / 4, kMaxBlocks);
-        PLX_DISPATCH_DT(grid->sh_dtype, DT, rays_fwd_kernel<DT, 16, 4, MODE, REC><<<nb, kWave, 0, s>>>(g, a));
-    }
+    PLX_DISPATCH_DT(grid->sh_dtype, DT, {
+        if (a.n_rays < kWaveRays<DT>) {
+            const unsigned nb = (unsigned)a.n_rays;
+            rays_fwd_kernel<DT, 64, 1, MODE, REC><<<nb, kWave, 0, s>>>(g, a);
+        } else {
+            const unsigned nb = (unsigned)std::min((a.n_rays + 3) / 4, kMaxBlocks);
+            rays_fwd_kernel<DT, 16, 4, MODE, REC><<<nb, kWave, 0, s>>>(g, a);
+        }
+    });
     return check_launch(fn);
 }
 
