@@ -494,7 +494,12 @@ __device__ __forceinline__ void march_rays(const GridDev &g, MarchLds<P, M> &sh,
             const double y = __shfl_up(incl, o, P);
             if (part >= o) incl += y;
         }
-        const float T0 = expf(-(float)(tau + (incl - tl)));
+        // depth of the ray's lanes before this one, taken from the scan and not
+        // as incl - tl: that is NaN where tl is infinite, and loses the lanes
+        // before a depth beyond 2^53 of theirs
+        double excl = __shfl_up(incl, 1, P);
+        if (part == 0) excl = 0.0;
+        const float T0 = expf(-(float)(tau + excl));
 #pragma unroll
         for (int a = 0; a < 3; ++a) C[a] += T0 * c[a];
         tau += __shfl(incl, P - 1, P);
