@@ -1472,7 +1472,11 @@ void seg_fwd_samples_kernel(GridDev g, BinArgs a) {
                     const double y = __shfl_up(incl, dd, kL);
                     if (part >= dd) incl += y;
                 }
-                const float T0 = expf(-(float)(incl - tau));
+                // the depth before the run from the scan, not as incl - tau,
+                // which is NaN after an infinite density
+                double excl = __shfl_up(incl, 1, kL);
+                if (part == 0) excl = 0.0;
+                const float T0 = expf(-(float)excl);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     C[c] *= T0;

@@ -66,6 +66,23 @@ def test_opaque_voxels_match_oracle(sh_dtype, value, n):
     check_training(B.make_ray_work(n), gg, oc, dc, tgt, rgb, check, ref)
 
 
+@pytest.mark.parametrize("sh_dtype", [B.PLX_F32, B.PLX_F16])
+@pytest.mark.parametrize("value", [float("inf"), 1e30])
+@pytest.mark.parametrize("n,samples", [(200, True), (700, True), (700, False), (9000, True)])
+def test_opaque_voxels_in_lists(sh_dtype, value, n, samples):
+    """The same over segment lists: replay, and the recorded backward below
+    and above 40 segments a brick (runs of a segment composed apart)."""
+    say("opaque voxels: lists", sh_dtype, value, n, samples)
+    og, gg = _opaque_pair(sh_dtype, value)
+    o, d = synth.random_rays(n, seed=94)
+    check = np.arange(n)[:: max(1, n // 4000)]
+    ref = O.render_fwd(og, o.numpy()[check], d.numpy()[check])[0]
+    oc, dc = o.cuda(), d.cuda()
+    bins = B.make_bins(gg.desc(), oc, dc, samples=samples)
+    assert (bins.n_seg >= 40 * bins.n_brick) == (n > 200)
+    check_training(bins, gg, oc, dc, synth.targets_uniform(n, seed=95).cuda(), torch.empty(n, 3, device="cuda"), check, ref)
+
+
 @pytest.mark.parametrize("w,h", [(30, 20), (300, 250), (1030, 770)])
 @pytest.mark.parametrize("value", [float("inf"), 1e30])
 def test_views_of_opaque_voxels_match_oracle(value, w, h):
