@@ -27,7 +27,8 @@ class RenderFn(torch.autograd.Function):
         if B.ray_order_grad(desc, n):
             # in ray order, keeping the occupied samples' values
             ctx.bins = None
-            work = B.make_ray_work(n, device=rays_o.device)
+            ctx.cap = B.ray_cap(n, desc)
+            work = B.make_ray_work(n, device=rays_o.device, cap=ctx.cap)
             B.plx_render_fwd_rays(desc, rays_o, rays_d, rgb, None, work, bg)
             ctx.save_for_backward(rays_o, rays_d, work.ray_ws, work.samp_ws)
         else:
@@ -45,7 +46,7 @@ class RenderFn(torch.autograd.Function):
         touched = torch.zeros(g.n_vox, dtype=torch.uint8, device=rays_o.device)
         grad_rgb = grad_rgb.contiguous().float()
         if ctx.bins is None:
-            work = B.RayWork(rays_o.shape[0], *saved, B.RAY_CAP)
+            work = B.RayWork(rays_o.shape[0], *saved, ctx.cap)
             B.plx_render_bwd_rays(g.desc(), rays_o, rays_d, grad_rgb, work, grad, touched, ctx.bg)
         else:
             B.plx_render_bwd(g.desc(), rays_o, rays_d, grad_rgb, saved[0], grad, touched, ctx.bg, bins=ctx.bins)

@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes
 from dataclasses import dataclass
+import math
 import os
 import re
 
@@ -526,9 +527,29 @@ def _bins_for(g: PlxGrid, rays_o, rays_d, bins: Bins | None) -> Bins:
     return make_bins(g, rays_o, rays_d) if bins is None else bins
 
 
-# Occupied samples of a ray that the ray-order passes keep (20 bytes each); a
-# ray with more has the rest evaluated again.
+# Occupied samples of a ray that the ray-order passes keep at most (20 bytes
+# each); a ray with more has the rest evaluated again.
 RAY_CAP = 512
+# Bytes of a batch's kept samples.  render() holds them until its backward, a
+# trainer two sets: at 512 a ray 300,000 rays take 3.1 GB, some eight times
+# their segment lists.  Evaluating a sample again costs little: forward and
+# backward with 512, 64, 22 and 1 samples kept per ray take 2392, 2430, 2450
+# and 2441 us for 300,000 rays (BF16, 512^3 at 5%), 554, 566, 569 and 571 for 65,537
+# (FP16, 256^3 at 10%), 288, 313, 327 and 330 for 16,000 (FP32, 512^3), which
+# still keep 419.
+RAY_SAMP_BYTES = 128 << 20
+
+
+def ray_cap(n_rays: int, g: PlxGrid | None = None) -> int:
+    """Samples kept per ray of a batch: RAY_CAP, or as many as RAY_SAMP_BYTES
+    holds, or as a ray of unit direction has on the grid's diagonal."""
+    cap = min(RAY_CAP, RAY_SAMP_BYTES // (20 * max(n_rays, 1)))
+    # (a grid that the call will refuse has no diagonal)
+    if g is not None and g.step > 0 and all(s > 0 for s in g.scale):
+        steps = math.sqrt(sum(((int(r) - 1) / s) ** 2 for r, s in zip(g.reso, g.scale))) / g.step
+        if steps < cap:
+            cap = int(steps) + 2
+    return max(1, cap)
 
 
 def ray_order(g: PlxGrid, n_rays: int) -> bool:
@@ -577,9 +598,11 @@ class RayWork:
 
 
 def make_ray_work(n_rays: int, ray_ws: torch.Tensor | None = None, samp_ws: torch.Tensor | None = None,
-                  _unused=None, device=None, cap: int = RAY_CAP) -> RayWork:
+                  _unused=None, device=None, cap: int | None = None) -> RayWork:
     """Scratch for n_rays rays, in the given buffers when they are large
-    enough, else in new ones."""
+    enough, else in new ones.  cap: samples kept per ray (ray_cap)."""
+    if cap is None:
+        cap = ray_cap(n_rays)
     need = plx_rays_ray_bytes(n_rays), plx_rays_samp_bytes(n_rays, cap)
     if ray_ws is None or ray_ws.numel() < need[0]:
         ray_ws = workspace(need[0], device)
@@ -629,7 +652,7 @@ def plx_render_train(g: PlxGrid, rays_o, rays_d, target, loss_scale, grad, touch
     made here (by ray_order) when not given."""
     n = rays_o.shape[0]
     if bins is None and ray_order(g, n):
-        bins = make_ray_work(n, device=rays_o.device)
+        bins = make_ray_work(n, device=rays_o.device, cap=ray_cap(n, g))
     if isinstance(bins, RayWork):
         plx_render_train_rays(g, rays_o, rays_d, target, loss_scale, grad, touched, loss_sum, bins, rgb_out, bg,
                               priors, grad_bg, events)
