@@ -10,23 +10,28 @@ from . import binding as B
 
 
 class RenderFn(torch.autograd.Function):
-    """rgb = RenderFn.apply(params, grid, rays_o, rays_d, bg).
+    """rgb = RenderFn.apply(params, grid, rays_o, rays_d, bg[, record]).
 
     ``params`` is the grid's FP32 record tensor [M, 32] (``grid.data`` for
     FP32 grids, ``grid.master`` for 16-bit ones); its gradient has the same
     record layout (slots 0..26 SH, slot 28 density).  The forward reads the
-    grid's stored records."""
+    grid's stored records.  record: whether a backward may follow (the
+    caller's grad mode, which a forward does not see); without one, or where
+    params need no gradient, no samples are kept."""
 
     @staticmethod
-    def forward(ctx, params, grid, rays_o, rays_d, bg):
+    def forward(ctx, params, grid, rays_o, rays_d, bg, record=True):
         n = rays_o.shape[0]
         rgb = torch.empty(n, 3, dtype=torch.float32, device=rays_o.device)
         desc = grid.desc()
         ctx.grid = grid
         ctx.bg = tuple(bg)
         if B.ray_order_grad(desc, n):
-            # in ray order, keeping the occupied samples' values
             ctx.bins = None
+            if not (record and ctx.needs_input_grad[0]):
+                B.plx_render_fwd_rays(desc, rays_o, rays_d, rgb, None, None, bg)
+                return rgb
+            # in ray order, keeping the occupied samples' values
             ctx.cap = B.ray_cap(n, desc)
             work = B.make_ray_work(n, device=rays_o.device, cap=ctx.cap)
             B.plx_render_fwd_rays(desc, rays_o, rays_d, rgb, None, work, bg)
@@ -50,10 +55,10 @@ class RenderFn(torch.autograd.Function):
             B.plx_render_bwd_rays(g.desc(), rays_o, rays_d, grad_rgb, work, grad, touched, ctx.bg)
         else:
             B.plx_render_bwd(g.desc(), rays_o, rays_d, grad_rgb, saved[0], grad, touched, ctx.bg, bins=ctx.bins)
-        return grad, None, None, None, None
+        return grad, None, None, None, None, None
 
 
 def render(grid, rays_o, rays_d, bg=(1.0, 1.0, 1.0)) -> torch.Tensor:
     """Differentiable render of a ray batch with respect to the grid's FP32
     records (set ``grid.param_records().requires_grad_()`` first)."""
-    return RenderFn.apply(grid.param_records(), grid, rays_o, rays_d, tuple(bg))
+    return RenderFn.apply(grid.param_records(), grid, rays_o, rays_d, tuple(bg), torch.is_grad_enabled())

@@ -6,7 +6,7 @@ import torch
 import synth
 from oracle import oracle as O
 from paper_2112_05131_amd import binding as B
-from paper_2112_05131_amd.autograd import render
+from paper_2112_05131_amd.autograd import RenderFn, render
 from tests.gpu_util import assert_grads_close, grad_mass, make_pair, say
 
 pytestmark = pytest.mark.gpu
@@ -33,3 +33,30 @@ def test_render_keeps_a_bounded_number_of_bytes():
     (rgb * Gc).sum().backward()
     gd, gs, _ = O.render_bwd(og, o.numpy(), d.numpy(), G.double().numpy())
     assert_grads_close(params.grad, gd, gs, "render", grad_mass(og, o.numpy(), d.numpy(), G.double().numpy()))
+
+
+@pytest.mark.parametrize("how", ["no_grad", "inference_mode", "frozen"])
+def test_nothing_is_kept_where_no_backward_follows(how):
+    """Under no_grad or inference mode, or with parameters that need no
+    gradient, render() allocates the image and little more, and returns the
+    same bits; RenderFn.apply with five arguments still records."""
+    say("render without backward", how)
+    _, gg = make_pair(synth.dense_random((40, 36, 44), seed=111, occupancy=0.3, ho_scale=0.2))
+    n = 5000
+    assert B.ray_order_grad(gg.desc(), n)
+    o, d = (x.cuda() for x in synth.random_rays(n, seed=112))
+    params = gg.param_records().requires_grad_()
+    full = render(gg, o, d)
+    assert full.requires_grad
+    five = RenderFn.apply(params, gg, o, d, (1.0, 1.0, 1.0))
+    five.sum().backward()
+    assert torch.equal(five, full) and params.grad.abs().sum() > 0
+    del five
+    params.requires_grad_(how != "frozen")
+    torch.cuda.synchronize()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    with {"no_grad": torch.no_grad, "inference_mode": torch.inference_mode, "frozen": torch.enable_grad}[how]():
+        rgb = render(gg, o, d)
+    assert torch.cuda.max_memory_allocated() - before <= 12 * n + 4096
+    assert not rgb.requires_grad and torch.equal(rgb, full.detach())
