@@ -9,6 +9,12 @@ import torch
 from . import binding as B
 
 
+def _aligned(t):
+    """t, or a copy where a saved-tensor hook handed back memory that is not
+    256-byte aligned, as the workspaces have to be."""
+    return t if t.data_ptr() % 256 == 0 and t.is_contiguous() else t.clone(memory_format=torch.contiguous_format)
+
+
 class RenderFn(torch.autograd.Function):
     """rgb = RenderFn.apply(params, grid, rays_o, rays_d, bg[, record]).
 
@@ -51,7 +57,7 @@ class RenderFn(torch.autograd.Function):
         touched = torch.zeros(g.n_vox, dtype=torch.uint8, device=rays_o.device)
         grad_rgb = grad_rgb.contiguous().float()
         if ctx.bins is None:
-            work = B.RayWork(rays_o.shape[0], *saved, ctx.cap)
+            work = B.RayWork(rays_o.shape[0], *map(_aligned, saved), ctx.cap)
             B.plx_render_bwd_rays(g.desc(), rays_o, rays_d, grad_rgb, work, grad, touched, ctx.bg)
         else:
             B.plx_render_bwd(g.desc(), rays_o, rays_d, grad_rgb, saved[0], grad, touched, ctx.bg, bins=ctx.bins)

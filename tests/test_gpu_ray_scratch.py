@@ -60,3 +60,30 @@ def test_nothing_is_kept_where_no_backward_follows(how):
         rgb = render(gg, o, d)
     assert torch.cuda.max_memory_allocated() - before <= 12 * n + 4096
     assert not rgb.requires_grad and torch.equal(rgb, full.detach())
+
+
+def test_saved_tensor_hooks_may_hand_back_unaligned_memory():
+    """Hooks that keep the saved tensors in one buffer at odd offsets (and
+    the rays at offsets of 4 bytes): the gradient is that without hooks."""
+    say("saved-tensor hooks")
+    _, gg = make_pair(synth.dense_random((20, 24, 22), seed=121, occupancy=0.5, ho_scale=0.2))
+    n = 3000
+    assert B.ray_order_grad(gg.desc(), n)
+    o, d = (x.cuda() for x in synth.random_rays(n, seed=122))
+    params = gg.param_records().requires_grad_()
+
+    def pack(t):
+        pool = torch.empty(t.numel() + 64, dtype=t.dtype, device=t.device)
+        off = 1 if t.dtype == torch.float32 else 12
+        pool[off:off + t.numel()] = t.reshape(-1)
+        return pool[off:off + t.numel()].view(t.shape)
+
+    grads = []
+    for hooks in (False, True):
+        params.grad = None
+        with torch.autograd.graph.saved_tensors_hooks(pack if hooks else lambda t: t, lambda t: t):
+            rgb = render(gg, o, d)
+        rgb.square().sum().backward()
+        grads.append(params.grad.clone())
+    scale = grads[0].abs().max().item()
+    assert scale > 0 and (grads[0] - grads[1]).abs().max().item() <= 1e-5 * scale
