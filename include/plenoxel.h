@@ -132,13 +132,14 @@ typedef struct plx_render_opts {
                                     dL/dC per ray (the upstream gradient of
                                     plx_bg_render_bwd) */
     void **kernel_events;        /* NULL, or 4 caller-created hipEvent_t that
-                                    the binned render calls record on the
-                                    stream (for timing): before the first
-                                    segment kernel, after the segment
-                                    forward, after the per-ray combine, and
-                                    after the segment backward (the last is
-                                    recorded at the end of forward-only
-                                    calls too) */
+                                    the binned render calls and those in
+                                    ray order (plx_render_*_rays) record on
+                                    the stream (for timing): before the
+                                    first kernel, after the forward, after
+                                    the per-ray combine (nothing in ray
+                                    order), and after the backward (the
+                                    last is recorded at the end of
+                                    forward-only calls too) */
 } plx_render_opts;
 
 /* ---------------------------------------------------------------- misc */

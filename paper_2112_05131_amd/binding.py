@@ -718,9 +718,9 @@ def plx_render_fwd_rays(g: PlxGrid, rays_o, rays_d, rgb_out, tau_out=None, work:
 
 
 def plx_render_bwd_rays(g: PlxGrid, rays_o, rays_d, grad_rgb, work: RayWork, grad, touched, bg=(1.0, 1.0, 1.0),
-                        priors: Priors | None = None, grad_bg=None):
+                        priors: Priors | None = None, grad_bg=None, events=None):
     n = rays_o.shape[0]
-    o = _opts(bg, priors, n, grad_bg)
+    o = _opts(bg, priors, n, grad_bg, events)
     _check(lib().plx_render_bwd_rays(ctypes.byref(g), ctypes.byref(o),
                                      _dptr(rays_o, "rays_o", torch.float32, 3 * n),
                                      _dptr(rays_d, "rays_d", torch.float32, 3 * n), n,

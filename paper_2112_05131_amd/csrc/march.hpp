@@ -541,5 +541,11 @@ inline int mark_event(void **events, int i, hipStream_t s, const char *fn) {
     PLX_CHECK_HIP(hipEventRecord(static_cast<hipEvent_t>(events[i]), s), fn);
     return PLX_OK;
 }
+// Events first..last-1.
+inline int mark_events(void **events, int first, int last, hipStream_t s, const char *fn) {
+    for (int i = first; i < last; ++i)
+        if (int rc = mark_event(events, i, s, fn)) return rc;
+    return PLX_OK;
+}
 
 }  // namespace plx

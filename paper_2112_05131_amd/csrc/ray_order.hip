@@ -581,12 +581,9 @@ int render_fwd_rays(const plx_grid *grid, const plx_render_opts *opts, const flo
     RayArgs a = base_args(opts, rays_o, rays_d, n_rays);
     a.rgb_out = rgb_out;
     a.tau_out = tau_out;
-    void **ev = opts->kernel_events;
-    int rc = mark_event(ev, 0, s, fn);
+    int rc = mark_event(opts->kernel_events, 0, s, fn);
     if (rc || (rc = launch_fwd<MODE_FWD, false>(grid, a, s, fn))) return rc;
-    for (int i = 1; i < 4; ++i)
-        if ((rc = mark_event(ev, i, s, fn))) return rc;
-    return PLX_OK;
+    return mark_events(opts->kernel_events, 1, 4, s, fn);
 }
 
 }  // namespace plx
@@ -663,7 +660,9 @@ int plx_render_fwd_rays(const plx_grid *grid, const plx_render_opts *opts, const
     if ((rc = attach_work(a, ray_ws, ray_ws_bytes, samp_ws, samp_ws_bytes, cap, fn))) return rc;
     a.rgb_out = rgb_out;
     a.tau_out = tau_out;
-    return launch_fwd<MODE_FWD, true>(grid, a, s, fn);
+    if ((rc = mark_event(opts->kernel_events, 0, s, fn))) return rc;
+    if ((rc = launch_fwd<MODE_FWD, true>(grid, a, s, fn))) return rc;
+    return mark_events(opts->kernel_events, 1, 4, s, fn);
 }
 
 int plx_render_bwd_rays(const plx_grid *grid, const plx_render_opts *opts, const float *rays_o,
@@ -683,7 +682,10 @@ int plx_render_bwd_rays(const plx_grid *grid, const plx_render_opts *opts, const
     a.grad_rgb = grad_rgb;
     a.grad = grad;
     a.touched = touched;
-    return launch_bwd<MODE_BWD>(grid, a, as_stream(stream), fn);
+    hipStream_t s = as_stream(stream);
+    if ((rc = mark_events(opts->kernel_events, 0, 3, s, fn))) return rc;
+    if ((rc = launch_bwd<MODE_BWD>(grid, a, s, fn))) return rc;
+    return mark_event(opts->kernel_events, 3, s, fn);
 }
 
 int plx_render_train_rays(const plx_grid *grid, const plx_render_opts *opts, const float *rays_o,
@@ -711,8 +713,7 @@ int plx_render_train_rays(const plx_grid *grid, const plx_render_opts *opts, con
     void **ev = opts->kernel_events;
     if ((rc = mark_event(ev, 0, s, fn))) return rc;
     if ((rc = launch_fwd<MODE_TRAIN, true>(grid, a, s, fn))) return rc;
-    if ((rc = mark_event(ev, 1, s, fn))) return rc;
-    if ((rc = mark_event(ev, 2, s, fn))) return rc;
+    if ((rc = mark_events(ev, 1, 3, s, fn))) return rc;
     if ((rc = launch_bwd<MODE_TRAIN>(grid, a, s, fn))) return rc;
     if ((a.pri.lambda_s != 0.0f || a.pri.lambda_b != 0.0f) && a.pri.loss) {
         rays_prior_kernel<<<(unsigned)std::min<int64_t>((n_rays + 255) / 256, 64), 256, 0, s>>>(a.vals, n_rays, a.pri);
