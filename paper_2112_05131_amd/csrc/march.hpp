@@ -208,9 +208,13 @@ __device__ __forceinline__ RaySkip ray_skip(const GridDev &g, const RayGeom &r) 
 
 // Number of further samples after sample k, as samples_behind before it, with
 // products by reciprocals for the quotients: the margin also covers the
-// rounding of the exit parameter (a few ulps of t_edge, in steps).
+// rounding of the exit parameter (a few ulps of t_edge, in steps).  The walks
+// that count and emit a ray's segments must cut the same ones, so this runs
+// without FMA contraction like the sample recipe: what the compiler would
+// fuse may differ from kernel to kernel.
 __device__ __forceinline__ int skip_box(const GridDev &g, const RayGeom &r, const RaySkip &q, int k,
                                         const int b[3], int R) {
+#pragma clang fp contract(off)
     const int nb[3] = {g.bx, g.by, g.bz};
     const float t = r.t_near + (float)k * g.step;
     float t_edge = __builtin_inff();
