@@ -148,3 +148,42 @@ def test_priors_validation_and_zero_weights():
     B.plx_render_bwd(gg.desc(), o.cuda(), d.cuda(), G, tau, grad, touched, priors=B.Priors(0.0, 0.0, 0.0, pl))
     torch.cuda.synchronize()
     assert torch.all(grad == 0) and torch.all(pl == 0) and int(touched.sum()) > 0
+
+
+@pytest.mark.parametrize("n", [1, 63, 4095, 4097, 9001])
+@pytest.mark.parametrize("route", ["state", "rays", "replay", "recorded"])
+def test_prior_losses_of_every_backward(route, n):
+    """The prior losses and gradients of each backward pass, at ray counts
+    around its number of workgroups: one sum per workgroup, whatever the
+    number of rays (or of the waves that hold a brick's samples) it has."""
+    say("prior losses", route, n)
+    og, gg = scene(271)
+    o, d = synth.random_rays(n, seed=272)
+    on, dn = o.numpy(), d.numpy()
+    G = np.random.default_rng(273).normal(size=(n, 3)) * 1e-2
+    oc, dc, Gc = o.cuda(), d.cuda(), torch.from_numpy(G).float().cuda()
+    desc, m = gg.desc(), gg.n_vox
+    grad = torch.zeros(m, 32, device="cuda")
+    touched = torch.zeros(m, dtype=torch.uint8, device="cuda")
+    pl = torch.zeros(2, dtype=torch.float64, device="cuda")
+    pri = B.Priors(LS, LB, EPS, pl)
+    rgb, tau = torch.empty(n, 3, device="cuda"), torch.empty(n, device="cuda")
+    if route == "state":
+        st = B.workspace(B.plx_render_state_bytes(n, 40))
+        B.plx_render_fwd_state(desc, oc, dc, rgb, tau, st, 40)
+        B.plx_render_bwd_state(desc, oc, dc, Gc, tau, st, 40, grad, touched, priors=pri)
+    elif route == "rays":
+        work = B.make_ray_work(n, cap=40)
+        B.plx_render_fwd_rays(desc, oc, dc, rgb, tau, work)
+        B.plx_render_bwd_rays(desc, oc, dc, Gc, work, grad, touched, priors=pri)
+    else:
+        bins = B.make_bins(desc, oc, dc, samples=route == "recorded")
+        B.plx_render_fwd(desc, oc, dc, rgb, tau)
+        B.plx_render_bwd(desc, oc, dc, Gc, tau, grad, touched, priors=pri, bins=bins)
+    Gd = Gc.cpu().double().numpy()
+    gd, gs, t_ref = O.render_bwd(og, on, dn, Gd)
+    ls_ref, lb_ref, gd_p, _ = O.regularisers(og, on, dn, LS, LB, EPS)
+    check_losses(pl, ls_ref, lb_ref)
+    md, ms = grad_mass(og, on, dn, Gd)
+    assert_touched_equal(touched, t_ref, route)
+    assert_grads_close(grad, gd + gd_p, gs, route, (md + prior_mass(og, on, dn, LS, LB, EPS), ms))
