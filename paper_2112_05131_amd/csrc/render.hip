@@ -2157,31 +2157,79 @@ __device__ __forceinline__ void raise_corners(unsigned *s_max, int p, float w) {
 // With one lane per segment on global memory the chains of index entries,
 // densities (one 4-byte read of a 128-byte record each) and the maxima
 // bounded both phases: 1M rays on 256^3 0.81 + 2.73 ms, now 0.14 + 0.19.
-template <int DT, int PHASE>
-__global__ __launch_bounds__(kThreads) void seg_weight_kernel(GridDev g, BinArgs a) {
+//
+// SPARSE, for bricks with few segments: a wave per brick, which first marks
+// the corners that its samples read and loads only these.  Loading them all
+// costs a brick 729 lines of 128 bytes however few rays cross it (5,000 rays
+// through a dense 256x256x128 grid, 6 segments a brick, 0.59 ms; so 0.24, and
+// 0.32 with a lane per segment).  In us, all / SPARSE, by segments a brick:
+// 16,000 bricks 5 499 / 228, 18 535 / 389, 24 653 / 447, 55 568 / 591, 71 677 /
+// 671, 184 675 / 890; 4,096 bricks 11 172 / 117, 29 180 / 167, 45 178 / 190.
+// Too few waves are left with fewer bricks: 1,733 92 / 67, 794 66 / 62, 832 with
+// 4 segments 63 / 68, 300 40 / 60.
+constexpr int64_t kSparseSegs = 32, kSparseBricks = 1024;
+template <int DT, int PHASE, bool SPARSE>
+__global__ __launch_bounds__(SPARSE ? kWave : kThreads) void seg_weight_kernel(GridDev g, BinArgs a) {
+    constexpr int T = SPARSE ? kWave : kThreads;
+    constexpr int kRounds = (kBrickVox + T - 1) / T;
     __shared__ float s_sigma[kBrickVox];
     __shared__ unsigned s_max[kBrickVox];
     __shared__ uint32_t s_occ[kBrickCells / 32];
+    __shared__ uint32_t s_need[SPARSE ? (kBrickVox + 31) / 32 : 1];
     if (blockIdx.x >= (unsigned)a.n_brick) return;
     const int t = threadIdx.x;
     const int64_t jo = a.blist[blockIdx.x];
     int b[3];
     brick_at(g, jo, b);
     const int b0[3] = {b[0] * PLX_BRICK, b[1] * PLX_BRICK, b[2] * PLX_BRICK};
-    int vid[(kBrickVox + kThreads - 1) / kThreads];
+    const int64_t seg0 = a.boff[jo * kLenClasses], seg1 = a.boff[(jo + 1) * kLenClasses];
+    // calls f(corner position of the cell, sample) for the occupied samples of a segment
+    auto walk = [&](const int4 &sg, auto &&f) {
+        float o[3], d[3];
+        load_ray_lane(a, sg.x, o, d);
+        RayGeom r;
+        ray_setup(g, o, d, r);
+        for (int k = sg.y; k <= sg.z; ++k) {
+            const Sample smp = sample_at(g, r, k);
+            const int lx = smp.cell[0] - b0[0], ly = smp.cell[1] - b0[1], lz = smp.cell[2] - b0[2];
+            if ((unsigned)lx >= PLX_BRICK || (unsigned)ly >= PLX_BRICK || (unsigned)lz >= PLX_BRICK) continue;
+            const int cell = (lx << 6) | (ly << 3) | lz;
+            if ((s_occ[cell >> 5] >> (cell & 31)) & 1u) f(lx * 81 + ly * 9 + lz, smp);
+        }
+    };
+    if (t < kBrickCells / 32) s_occ[t] = g.occ[brick_id(g, b) * (kBrickCells / 32) + t];
+    if constexpr (SPARSE) {
+        if (t < (kBrickVox + 31) / 32) s_need[t] = 0u;
+        __syncthreads();
+        for (int64_t i = seg0 + t; i < seg1; i += T) {
+            const int4 sg = a.bseg[i];
+            if (!seg_valid(a, sg, a.n_seg)) continue;
+            int cur = -1;
+            walk(sg, [&](int p, const Sample &) {
+                if (p == cur) return;
+                cur = p;
 #pragma unroll
-    for (int rr = 0; rr * kThreads < kBrickVox; ++rr) {
-        const int p = t + rr * kThreads;
+                for (int c = 0; c < 8; ++c) {
+                    const int q = p + corner_position(c);
+                    atomicOr(&s_need[q >> 5], 1u << (q & 31));
+                }
+            });
+        }
+        __syncthreads();
+    }
+    int vid[kRounds];
+#pragma unroll
+    for (int rr = 0; rr < kRounds; ++rr) {
+        const int p = t + rr * T;
         vid[rr] = -1;
-        if (p < kBrickVox) {
+        if (p < kBrickVox && (!SPARSE || ((s_need[p >> 5] >> (p & 31)) & 1u))) {
             const int X = b0[0] + p / 81, Y = b0[1] + (p / 9) % 9, Z = b0[2] + p % 9;
             if (X < g.nx && Y < g.ny && Z < g.nz) vid[rr] = g.index[((int64_t)X * g.ny + Y) * g.nz + Z];
         }
     }
-    if (t < kBrickCells / 32) s_occ[t] = g.occ[brick_id(g, b) * (kBrickCells / 32) + t];
 #pragma unroll
-    for (int rr = 0; rr * kThreads < kBrickVox; ++rr) {
-        const int p = t + rr * kThreads;
+    for (int rr = 0; rr < kRounds; ++rr) {
+        const int p = t + rr * T;
         if (p < kBrickVox) {
             s_sigma[p] = vid[rr] >= 0 ? rec_sigma<DT>(g.data, vid[rr]) : 0.0f;
             s_max[p] = 0u;
@@ -2189,24 +2237,13 @@ __global__ __launch_bounds__(kThreads) void seg_weight_kernel(GridDev g, BinArgs
     }
     __syncthreads();
 
-    const int64_t seg0 = a.boff[jo * kLenClasses], seg1 = a.boff[(jo + 1) * kLenClasses];
-    for (int64_t i = seg0 + t; i < seg1; i += kThreads) {
+    for (int64_t i = seg0 + t; i < seg1; i += T) {
         const int4 sg = a.bseg[i];
         if (!seg_valid(a, sg, a.n_seg)) continue;
-        float o[3], d[3];
-        load_ray_lane(a, sg.x, o, d);
-        RayGeom r;
-        ray_setup(g, o, d, r);
         double tau = PHASE == 0 ? 0.0 : a.tau_in[sg.w];
         int cur = -1;      // corner position of the current cell's lower corner
         float wmax = 0.0f; // largest weight of the run of samples in it
-        for (int k = sg.y; k <= sg.z; ++k) {
-            const Sample smp = sample_at(g, r, k);
-            const int lx = smp.cell[0] - b0[0], ly = smp.cell[1] - b0[1], lz = smp.cell[2] - b0[2];
-            if ((unsigned)lx >= PLX_BRICK || (unsigned)ly >= PLX_BRICK || (unsigned)lz >= PLX_BRICK) continue;
-            const int cell = (lx << 6) | (ly << 3) | lz;
-            if (!((s_occ[cell >> 5] >> (cell & 31)) & 1u)) continue;
-            const int p = lx * 81 + ly * 9 + lz;
+        walk(sg, [&](int p, const Sample &smp) {
             const float wx[2] = {1.0f - smp.f[0], smp.f[0]}, wy[2] = {1.0f - smp.f[1], smp.f[1]},
                         wz[2] = {1.0f - smp.f[2], smp.f[2]};
             float sp = 0.0f;
@@ -2224,7 +2261,7 @@ __global__ __launch_bounds__(kThreads) void seg_weight_kernel(GridDev g, BinArgs
                 wmax = fmaxf(wmax, wk);
             }
             tau += (double)sd;
-        }
+        });
         if (PHASE == 0) a.tau_seg[sg.w] = tau;
         else if (cur >= 0) raise_corners(s_max, cur, wmax);
     }
@@ -2233,8 +2270,8 @@ __global__ __launch_bounds__(kThreads) void seg_weight_kernel(GridDev g, BinArgs
     // non-negative floats order as their bit patterns; wmax only grows, so a
     // value already at least the candidate makes the atomic unnecessary
 #pragma unroll
-    for (int rr = 0; rr * kThreads < kBrickVox; ++rr) {
-        const int p = t + rr * kThreads;
+    for (int rr = 0; rr < kRounds; ++rr) {
+        const int p = t + rr * T;
         if (p >= kBrickVox || vid[rr] < 0) continue;
         const unsigned cand = s_max[p];
         unsigned *q = reinterpret_cast<unsigned *>(a.wmax) + vid[rr];
@@ -2700,11 +2737,18 @@ int render_binned(const plx_grid *grid, BinArgs a, hipStream_t s, const char *fn
     if ((rc = mark_event(a.events, 0, s, fn))) return rc;
     if constexpr (MODE == MODE_MAXW) {
         if (a.n_seg == 0) return PLX_OK;
-        PLX_DISPATCH_DT(grid->sh_dtype, DT, seg_weight_kernel<DT, 0><<<(unsigned)a.n_brick, kThreads, 0, s>>>(g, as));
+        const bool sparse = a.n_brick >= kSparseBricks && a.n_seg < kSparseSegs * a.n_brick;
+        PLX_DISPATCH_DT(grid->sh_dtype, DT, {
+            if (sparse) seg_weight_kernel<DT, 0, true><<<(unsigned)a.n_brick, kWave, 0, s>>>(g, as);
+            else seg_weight_kernel<DT, 0, false><<<(unsigned)a.n_brick, kThreads, 0, s>>>(g, as);
+        });
         if ((rc = check_launch(fn))) return rc;
         seg_combine_kernel<MODE><<<(unsigned)nbr, kThreads, 0, s>>>(a);
         if ((rc = check_launch(fn))) return rc;
-        PLX_DISPATCH_DT(grid->sh_dtype, DT, seg_weight_kernel<DT, 1><<<(unsigned)a.n_brick, kThreads, 0, s>>>(g, as));
+        PLX_DISPATCH_DT(grid->sh_dtype, DT, {
+            if (sparse) seg_weight_kernel<DT, 1, true><<<(unsigned)a.n_brick, kWave, 0, s>>>(g, as);
+            else seg_weight_kernel<DT, 1, false><<<(unsigned)a.n_brick, kThreads, 0, s>>>(g, as);
+        });
         return check_launch(fn);
     }
     if (a.n_seg > 0) {

@@ -27,3 +27,22 @@ def test_max_weight_brick_edges(reso, occ, nrays, hi, sh_dtype):
     assert (ref.max() > 0) == (hi > 0)
     check_wmax(gpu_max_weight(gg, o, d), ref, "edges")
     assert np.isfinite(ref).all()
+
+
+@pytest.mark.parametrize("sh_dtype", [B.PLX_F32, B.PLX_BF16])
+@pytest.mark.parametrize("reso,occ,nrays,sparse", [((100, 90, 99), 0.6, 700, True), ((97, 97, 97), 1.0, 2500, True),
+                                                   ((73, 121, 82), 0.4, 9000, False), ((65, 65, 66), 1.0, 900, False)])
+def test_max_weight_with_few_segments_a_brick(reso, occ, nrays, sparse, sh_dtype):
+    """Both sides of the rule for marking the corners first (1,024 bricks with
+    fewer than 32 segments each), partial bricks among them, in one call and
+    in two.  The bound is that of the other tests of the weight pass."""
+    say("weight: few segments", reso, occ, nrays, sh_dtype)
+    sv = synth.dense_random(reso, seed=73, occupancy=occ, sigma_lo=-5.0, sigma_hi=30.0)
+    og, gg = make_pair(sv, sh_dtype=sh_dtype)
+    o, d = synth.random_rays(nrays, seed=74)
+    bins = B.make_bins(gg.desc(), o.cuda(), d.cuda(), samples=False)
+    assert (bins.n_brick >= 1024 and bins.n_seg < 32 * bins.n_brick) == sparse
+    ref = O.max_weight(og, o.numpy(), d.numpy())
+    assert ref.max() > 0
+    check_wmax(gpu_max_weight(gg, o, d), ref, "one call")
+    check_wmax(gpu_max_weight(gg, o, d, batches=2), ref, "two calls")
