@@ -592,7 +592,8 @@ int plx_scene_table_set(const plx_grid *scenes, int32_t n_scenes, void *table, i
 
 /* Bytes of the queue buffer of plx_render_views: device memory, 256-byte
  * aligned, zero-filled once before its first use.  It holds the sticky status
- * word of the launches that were given it. */
+ * word of the launches that were given it, and the tile counter of the one
+ * that runs. */
 #define PLX_VIEWS_QUEUE_BYTES 256
 
 /* Renders a batch of novel views of resident scenes (the forward model of
