@@ -440,8 +440,9 @@ int plx_bins_verify(const plx_grid *grid, const plx_bins *bins, plx_stream strea
  * is composited with Eq. (1) and the background is added with the remaining
  * transmittance.  Outputs (device float32): rgb_out[n_rays][3] and tau_out[n_rays]
  * = sum sigma_k delta_k (the optical depth, so T_final = exp(-tau)).  tau_out
- * may be NULL.  bins: the segment lists of these rays (plx_bins); batches
- * below 786,432 rays are marched in ray order, as by plx_render_fwd_rays. */
+ * may be NULL.  bins: the segment lists of these rays (plx_bins); where the
+ * march of plx_render_fwd_rays is the faster one (most batches below 786,432
+ * rays) they are not read. */
 int plx_render_fwd(const plx_grid *grid, const plx_render_opts *opts, const float *rays_o,
                    const float *rays_d, int64_t n_rays, const plx_bins *bins, float *rgb_out,
                    float *tau_out, plx_stream stream);

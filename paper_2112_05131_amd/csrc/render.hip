@@ -1158,9 +1158,6 @@ constexpr int kWalkRun = 8;       // consecutive samples a walking lane tests at
 // segments per brick; even at 262,144 rays, about 36; 2.66 against 1.81 ms
 // at 1M rays, 138)
 constexpr int64_t kFwdParMinSegs = 40;
-// Rays from which plx_render_fwd takes its lists rather than the march in ray
-// order (the reason stands there).
-constexpr int64_t kListFwdRays = 3 << 18;
 
 template <int DT> struct FwdStage {
     static constexpr int kHalves = DT == PLX_F32 ? 2 : 1;
@@ -2973,6 +2970,27 @@ int static_scratch(void **out, const char *fn) {
     return PLX_OK;
 }
 
+// Whether a batch whose lists exist is rendered over them (the march in ray
+// order needs none).  Ray order / lists in us:
+// - 16-bit records: a workgroup stages its brick's records once, which pays
+//   when many samples share them and there are bricks enough to fill the chip.
+//   Samples per brick 1,150 (512^3 at 5%) 1044 / 1517, 1,580 (dense 128^3) 358 / 386,
+//   1,860 (256x256x128) 1151 / 1210; 2,000 (200^3) 1669 / 1430, 2,840 (256x256x128)
+//   1730 / 1542, 4,150 (128^3 from inside) 812 / 668, 19,100 (128^3) 3548 / 2010; but
+//   with 1,728 bricks 697 / 725 at 10,500, 1,000 bricks 1023 / 1275 at 39,300.
+// - FP32: the bricks in order share what the caches hold, which counts when
+//   the grid's records do not fit (8,192 bricks with stored corners are some
+//   512 MB): 98,304 rays on 512^3 417 / 325, 400,000 984 / 911, 786,000 on dense 200^3
+//   8961 / 7722; 65,536 226 / 235; with 4,096 bricks 4939 / 4743 at 786,000 rays of
+//   dense 128^3, 3194 / 3190 at 200,000 from inside, 5,000 bricks 1195 / 1330.
+// - from 786,432 rays on the lists, whose order does not depend on the rays'
+//   (512^3, 1M rays: 2.12 / 1.92 ms, shuffled 2.46 / 1.92).
+bool forward_over_lists(int32_t sh_dtype, int64_t n_rays, const plx_bins *bins) {
+    if (n_rays >= 3 << 18) return true;
+    if (sh_dtype == PLX_F32) return n_rays >= 3 << 15 && bins->n_brick >= 1 << 13;
+    return bins->n_brick >= 1 << 11 && bins->n_samp >= 2000 * bins->n_brick;
+}
+
 }  // namespace
 }  // namespace plx
 
@@ -3094,13 +3112,7 @@ int plx_render_fwd(const plx_grid *grid, const plx_render_opts *opts, const floa
     for (int i = 0; i < 3; ++i) a.bg[i] = opts->background[i];
     a.bg_rgb = opts->background_rgb;
     a.grad_bg = opts->grad_background;
-    // The march in ray order needs no lists and is the faster one up to large
-    // batches: an 800x800 image of 512^3 0.97 against 1.34 ms (FP32), 0.59
-    // against 1.44 (FP16); 65,536 FP16 rays on 256^3 0.14 against 0.37.  At 1M
-    // rays, whose lists exist already, the two are even (512^3: 2.12 against
-    // 1.92 ms FP32, 1.36 against 1.62 FP16; shuffled 2.46 against 1.92 and
-    // 1.80 against 1.60): there the lists are used.
-    if (n_rays < kListFwdRays)
+    if (!forward_over_lists(grid->sh_dtype, n_rays, bins))
         return render_fwd_rays(grid, opts, rays_o, rays_d, n_rays, rgb_out, tau_out, as_stream(stream), fn);
     return render_binned<MODE_FWD>(grid, a, as_stream(stream), fn);
 }
