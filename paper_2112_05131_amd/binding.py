@@ -558,12 +558,27 @@ def ray_order(g: PlxGrid, n_rays: int) -> bool:
     every ray sends a line of atomics per voxel it crosses, and nothing is
     binned, counted or read back; the lists merge the rays of a brick.  The
     batch's occupied brick crossings are estimated by n_rays times the bricks
-    along a ray times the share of occupied voxels.  Ray order / lists with
-    their binning (us, FP32): 5000 rays on 256^3 at 10% (16,000 crossings) 175 /
-    700, 5000 on a dense 64^3 (40,000) 164 / 590, 16,000 on 512^3 at 5% (51,000)
-    328 / 860; beyond the line it is only somewhat ahead or behind: 5000
-    inside a dense 128^3 (80,000) 599 / 960, 20,011 through a dense 256x256x128
-    (530,000) 1836 / 2180, 49,152 there 4129 / 3300."""
+    along a ray times the share of occupied voxels; the line is 196,608.
+
+    Below it ray order takes at most half the time.  Ray order / lists with
+    their binning (us, FP32; crossings): 5000 rays on 256^3 at 10% (48,000) 129 /
+    529, on a dense 64^3 (120,000) 127 / 503, 2500 inside a dense 128^3 (120,000)
+    286 / 615, 20,000 on 512^3 at 5% (192,000) 317 / 682, 2500 through a dense
+    256x256x128 (200,000) 250 / 541.
+
+    Above it ray order is still ahead, up to the recorded backward of 65,536
+    rays (5000 inside the 128^3 532 / 822, 20,000 through the 256x256x128 1661 / 2079,
+    40,000 on 512^3 495 / 791; 80,000 there 837 / 1484, but 713 / 708 on 256^3 at
+    10% and 6481 / 3446 through the 256x256x128).  The lists stay there because
+    ray order adds a sample's terms in another order, which a gain below 2 was
+    not held to be worth: where a density lies at 0 the last bit of one step
+    decides a gate of the next, and with many samples one may.  Two steps of
+    20,011 rays through the 256x256x128 grid gave densities that differ by 1e-3
+    of the largest in one of eight seeds (else by 1e-6), of 5000 inside the
+    128^3 by 4e-6, below the line (64^3, 256^3) by 4e-7; runs of the same order
+    differ by 2e-7.  Ray order is not the less exact of the two (densities after a
+    step against 64 bits, relative: 6.8e-8 and 7.6e-8 through the 256x256x128,
+    3.5e-8 and 4.0e-8 inside the 128^3, 8.8e-8 and 9.8e-8 on 64^3)."""
     b = [-(-(int(r) - 1) // 8) for r in g.reso]
     cells = int(g.reso[0]) * int(g.reso[1]) * int(g.reso[2])
     return n_rays * sum(b) * int(g.n_vox) < 3 * 65536 * cells
@@ -571,15 +586,16 @@ def ray_order(g: PlxGrid, n_rays: int) -> bool:
 
 def ray_order_grad(g: PlxGrid, n_rays: int) -> bool:
     """As ray_order, for a separate forward and backward pass, where lists
-    also cost a forward of their own: ray order while few rays cross a brick
-    (x = n_rays times the bricks along a ray over all bricks), and for small
-    batches, whose lists are mostly fixed costs.  Ray order / lists in us:
-    5000 rays on 64^3 164 / 277; sparse grids (up to a quarter occupied):
-    300,000 on 512^3 at 5% (x = 73) 2603 / 4004 (BF16), 230,400 on 380^3 at 4%
-    (100) 1342 / 1723 and at 10% 2966 / 3124 (at x = 130 3717 / 3439), 64,000 on
-    128^3 at 12% (250) 447 / 617; dense grids: 128^3 from outside (75) 907 /
-    1197, but 16,384 from inside it (64) 1646 / 1440 and 49,152 through a
-    256x256x128 (77) 4129 / 3302."""
+    also cost a forward of their own and no step follows: ray order while few
+    rays cross a brick (x = n_rays times the bricks along a ray over all
+    bricks), and for small batches, whose lists are mostly fixed costs.  Ray
+    order / lists in us: 5000 rays on 64^3 132 / 214; sparse grids (up to a
+    quarter occupied): 300,000 on 512^3 at 5% (x = 73) 2442 / 3762 (BF16), 400,000
+    (98) 3184 / 3174, 230,400 on 380^3 at 10% (100) 2852 / 2873, 300,000 (130) 3635 /
+    3190, 100,000 on 256^3 at 10% (98) 801 / 858 (FP16), 64,000 on 128^3 at 12%
+    (250) 384 / 442; dense grids: 128^3 from outside (47) 505 / 759, from inside (31)
+    804 / 906, but 16,384 there (64) 1551 / 1370; 20,000 through a 256x256x128 (33)
+    1674 / 2442, 49,152 (80) 4092 / 3704."""
     b = [-(-(int(r) - 1) // 8) for r in g.reso]
     sparse = 4 * int(g.n_vox) < int(g.reso[0]) * int(g.reso[1]) * int(g.reso[2])
     return (n_rays < (65536 if sparse else 8192)
@@ -594,11 +610,12 @@ class RayWork:
         self.n_rays, self.ray_ws, self.samp_ws, self.cap = n_rays, ray_ws, samp_ws, cap
 
     def buffers(self):
+        """As of Bins, which may take the buffers over and hand them back."""
         return [self.ray_ws, self.samp_ws, None]
 
 
 def make_ray_work(n_rays: int, ray_ws: torch.Tensor | None = None, samp_ws: torch.Tensor | None = None,
-                  _unused=None, device=None, cap: int | None = None) -> RayWork:
+                  device=None, cap: int | None = None) -> RayWork:
     """Scratch for n_rays rays, in the given buffers when they are large
     enough, else in new ones.  cap: samples kept per ray (ray_cap)."""
     if cap is None:
@@ -613,8 +630,11 @@ def make_ray_work(n_rays: int, ray_ws: torch.Tensor | None = None, samp_ws: torc
 
 def plx_render_fwd(g: PlxGrid, rays_o, rays_d, rgb_out, tau_out=None, bg=(1.0, 1.0, 1.0),
                    bins: Bins | None = None, events=None):
-    """bins: the batch's segment lists where they exist already (without them
-    the rays are marched in ray order, which needs none)."""
+    """bins: the batch's segment lists where they exist already.  Without them
+    the rays are marched in ray order, which needs none; only very large
+    batches of scattered rays on dense 16-bit grids would gain from lists made
+    for the purpose (640,000 on 128^3 2.96 ms, over lists with their binning
+    2.22; an image of as many pixels 1.53 and 2.66)."""
     n = rays_o.shape[0]
     o = _opts(bg, None, n, None, events)
     if bins is None:

@@ -309,7 +309,7 @@ class Trainer:
                 o, d, t = sampler.next_batch(out=bb)
                 desc = self.grid.desc()
                 if B.ray_order(desc, o.shape[0]):
-                    b = B.make_ray_work(o.shape[0], *bufs[slot], device=o.device, cap=B.ray_cap(o.shape[0], desc))
+                    b = B.make_ray_work(o.shape[0], *bufs[slot][:2], o.device, B.ray_cap(o.shape[0], desc))
                 else:
                     b = B.make_bins(desc, o, d, *bufs[slot], samples=recorded_backward(o.shape[0]))
                 bufs[slot] = b.buffers()
