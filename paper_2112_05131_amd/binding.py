@@ -563,8 +563,8 @@ def ray_order(g: PlxGrid, n_rays: int) -> bool:
     Below it ray order takes at most half the time.  Ray order / lists with
     their binning (us, FP32; crossings): 5000 rays on 256^3 at 10% (48,000) 129 /
     529, on a dense 64^3 (120,000) 127 / 503, 2500 inside a dense 128^3 (120,000)
-    286 / 615, 20,000 on 512^3 at 5% (192,000) 317 / 682, 2500 through a dense
-    256x256x128 (200,000) 250 / 541.
+    286 / 615, 20,000 on 512^3 at 5% (192,000) 317 / 682, 1000 through a dense
+    256x256x128 (80,000) 129 / 457.
 
     Above it ray order is still ahead, up to the recorded backward of 65,536
     rays (5000 inside the 128^3 532 / 822, 20,000 through the 256x256x128 1661 / 2079,
