@@ -365,15 +365,23 @@ template <int DT, int P, int M> struct Evaluator {
 // of a ray, the colour before the background is added and the optical depth.
 // rec(i, k, v) gets the i-th occupied sample of a ray (sample index k, values
 // v) in the lane that composes it, when REC::kOn; the ray's number of occupied
-// samples goes to *count.  Called by the whole wave.
+// samples goes to *count.  With REC::kOpaque a sample adds at most kOpaque to
+// tau, and what it has beyond that goes to *over.  Called by the whole wave.
 struct NoRecord {
-    static constexpr bool kOn = false;
+    static constexpr bool kOn = false, kOpaque = false;
     __device__ __forceinline__ void operator()(int, int, const float4 &) const {}
 };
 
+// Optical depth beyond which FP32 has no transmittance left (expf(-104) is 0).
+// Depths summed from samples cut here give the same transmittances, and can be
+// taken off the sum again sample by sample, which a sum that an infinite (or
+// huge) one has gone into cannot: the reverse walk of a ray needs that.
+constexpr float kOpaque = 256.0f;
+
 template <int DT, int P, int M, class REC>
 __device__ __forceinline__ void march_rays(const GridDev &g, MarchLds<P, M> &sh, const RayGeom &r, int n,
-                                           float C[3], double &tau, const REC &rec, int *count = nullptr) {
+                                           float C[3], double &tau, const REC &rec, int *count = nullptr,
+                                           double *over = nullptr) {
     static_assert(P * M <= 64 && (P & (P - 1)) == 0, "window");
     int n_occ = 0;
     const int part = lane_id() % P, slot = lane_id() / P;
@@ -488,7 +496,13 @@ __device__ __forceinline__ void march_rays(const GridDev &g, MarchLds<P, M> &sh,
                     c[0] += wk * fmaxf(v.y, 0.0f);
                     c[1] += wk * fmaxf(v.z, 0.0f);
                     c[2] += wk * fmaxf(v.w, 0.0f);
-                    tl += (double)sd;
+                    if constexpr (REC::kOpaque) {
+                        const float cut = fminf(sd, kOpaque);
+                        if (over && sd > cut) *over += (double)sd - (double)cut;
+                        tl += (double)cut;
+                    } else {
+                        tl += (double)sd;
+                    }
                 }
             }
         }
@@ -514,7 +528,13 @@ __device__ __forceinline__ void march_rays(const GridDev &g, MarchLds<P, M> &sh,
 #pragma unroll
         for (int a = 0; a < 3; ++a) C[a] += __shfl_xor(C[a], o, P);
     }
-    if constexpr (REC::kOn) *count = n_occ;
+    if constexpr (REC::kOn) {
+        *count = n_occ;
+        if (over) {
+#pragma unroll
+            for (int o = 1; o < P; o <<= 1) *over += __shfl_xor(*over, o, P);
+        }
+    }
 }
 
 // ------------------------------------------------------------ host helpers

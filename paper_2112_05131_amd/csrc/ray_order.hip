@@ -26,11 +26,15 @@ namespace plx {
 namespace {
 
 enum { MODE_FWD = 0, MODE_BWD = 1, MODE_TRAIN = 2 };
+// What a forward keeps of its samples: nothing; the first ones of each ray;
+// these, while it also returns depths (an instance of its own, as the sum of
+// what kOpaque cuts off costs registers).
+enum { REC_NONE = 0, REC_SAMPLES = 1, REC_DEPTHS = 2 };
 
 // Per-ray values that a forward call hands to its backward.
 struct RayVals {
     float4 g;      // dL/dC
-    double tau;    // optical depth
+    double tau;    // optical depth, of samples cut at kOpaque
     double loss;   // the ray's share of the loss
     double cauchy, beta;  // and of the priors' (backward; written where their losses are wanted)
 };
@@ -69,7 +73,7 @@ __device__ __forceinline__ void load_ray(const RayArgs &a, int64_t ray, float o[
 
 // Records the first st_cap occupied samples of a ray.
 struct Record {
-    static constexpr bool kOn = true;
+    static constexpr bool kOn = true, kOpaque = true;
     int *kidx;
     float4 *vals;
     int cap;
@@ -83,7 +87,7 @@ struct Record {
 
 // Marches the wave's 64 / P rays; `ray` is the lane's.  TRAIN also forms the
 // loss and dL/dC = 2 loss_scale (C - target).
-template <int DT, int P, int M, int MODE, bool REC>
+template <int DT, int P, int M, int MODE, int REC>
 __device__ __forceinline__ void forward_rays(const GridDev &g, const RayArgs &a, MarchLds<P, M> &sh, int64_t ray) {
     const bool in = ray < a.n_rays;
     float o[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 1.f};
@@ -93,10 +97,12 @@ __device__ __forceinline__ void forward_rays(const GridDev &g, const RayArgs &a,
     march_basis(sh, d);
     float C[3];
     double tau;
-    if constexpr (REC) {
+    double over = 0.0;  // what tau lacks of the optical depth
+    if constexpr (REC != REC_NONE) {
         int count = 0;
         const int64_t base = in ? ray * a.st_cap : 0;
-        march_rays<DT>(g, sh, r, n, C, tau, Record{a.st_kidx + base, a.st_vals + base, a.st_cap}, &count);
+        const Record rec{a.st_kidx + base, a.st_vals + base, a.st_cap};
+        march_rays<DT>(g, sh, r, n, C, tau, rec, &count, REC == REC_DEPTHS ? &over : nullptr);
         if (in && lane_id() % P == 0) a.st_count[ray] = count;
     } else {
         march_rays<DT>(g, sh, r, n, C, tau, NoRecord{});
@@ -118,8 +124,8 @@ __device__ __forceinline__ void forward_rays(const GridDev &g, const RayArgs &a,
         }
     }
     if (MODE == MODE_FWD) {
-        if (a.tau_out) a.tau_out[ray] = (float)tau;
-        if (REC && a.vals) a.vals[ray].tau = tau;
+        if (a.tau_out) a.tau_out[ray] = (float)(tau + over);
+        if (REC != REC_NONE && a.vals) a.vals[ray].tau = tau;
     } else {
         RayVals v = {};
         v.g = make_float4(gr[0], gr[1], gr[2], 0.0f);
@@ -134,7 +140,7 @@ __device__ __forceinline__ void forward_rays(const GridDev &g, const RayArgs &a,
 }
 
 // Forward march of 64 / P rays per wave (one wave per workgroup).
-template <int DT, int P, int M, int MODE, bool REC>
+template <int DT, int P, int M, int MODE, int REC>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void rays_fwd_kernel(GridDev g, RayArgs a) {
     __shared__ MarchLds<P, M> sh;
@@ -206,7 +212,7 @@ __device__ __forceinline__ void window_bwd(const GridDev &g, const RayArgs &a, B
     const float sd = on ? fmaxf(v.x, 0.0f) * sm.delta : 0.0f;
     // optical depth after the sample (the samples above it in the window
     // taken off the end), and before it
-    double dsum = (double)sd;
+    double dsum = (double)(a.vals ? fminf(sd, kOpaque) : sd);
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
         const double t = __shfl_down(dsum, o);
@@ -472,7 +478,7 @@ template <int DT> constexpr int64_t kWaveRays = DT == PLX_F32 ? 3 << 15 : 3 << 1
 // 2^32 threads).
 constexpr int64_t kMaxBlocks = 1 << 25;
 
-template <int MODE, bool REC>
+template <int MODE, int REC>
 int launch_fwd(const plx_grid *grid, const RayArgs &a, hipStream_t s, const char *fn) {
     const GridDev g = to_dev(grid);
     PLX_DISPATCH_DT(grid->sh_dtype, DT, {
@@ -485,6 +491,11 @@ int launch_fwd(const plx_grid *grid, const RayArgs &a, hipStream_t s, const char
         }
     });
     return check_launch(fn);
+}
+
+// The forward that records.
+int launch_record(const plx_grid *grid, const RayArgs &a, hipStream_t s, const char *fn) {
+    return a.tau_out ? launch_fwd<MODE_FWD, REC_DEPTHS>(grid, a, s, fn) : launch_fwd<MODE_FWD, REC_SAMPLES>(grid, a, s, fn);
 }
 
 // Workgroups of a backward whose prior losses no per-ray values hold: as many
@@ -602,7 +613,7 @@ int render_fwd_rays(const plx_grid *grid, const plx_render_opts *opts, const flo
     a.rgb_out = rgb_out;
     a.tau_out = tau_out;
     int rc = mark_event(opts->kernel_events, 0, s, fn);
-    if (rc || (rc = launch_fwd<MODE_FWD, false>(grid, a, s, fn))) return rc;
+    if (rc || (rc = launch_fwd<MODE_FWD, REC_NONE>(grid, a, s, fn))) return rc;
     return mark_events(opts->kernel_events, 1, 4, s, fn);
 }
 
@@ -630,7 +641,7 @@ int plx_render_fwd_state(const plx_grid *grid, const plx_render_opts *opts, cons
     if ((rc = attach_state(a, state, state_bytes, cap, fn))) return rc;
     a.rgb_out = rgb_out;
     a.tau_out = tau_out;
-    return launch_fwd<MODE_FWD, true>(grid, a, as_stream(stream), fn);
+    return launch_record(grid, a, as_stream(stream), fn);
 }
 
 int plx_render_bwd_state(const plx_grid *grid, const plx_render_opts *opts, const float *rays_o,
@@ -681,7 +692,7 @@ int plx_render_fwd_rays(const plx_grid *grid, const plx_render_opts *opts, const
     a.rgb_out = rgb_out;
     a.tau_out = tau_out;
     if ((rc = mark_event(opts->kernel_events, 0, s, fn))) return rc;
-    if ((rc = launch_fwd<MODE_FWD, true>(grid, a, s, fn))) return rc;
+    if ((rc = launch_record(grid, a, s, fn))) return rc;
     return mark_events(opts->kernel_events, 1, 4, s, fn);
 }
 
@@ -732,7 +743,7 @@ int plx_render_train_rays(const plx_grid *grid, const plx_render_opts *opts, con
     hipStream_t s = as_stream(stream);
     void **ev = opts->kernel_events;
     if ((rc = mark_event(ev, 0, s, fn))) return rc;
-    if ((rc = launch_fwd<MODE_TRAIN, true>(grid, a, s, fn))) return rc;
+    if ((rc = launch_fwd<MODE_TRAIN, REC_SAMPLES>(grid, a, s, fn))) return rc;
     if ((rc = mark_events(ev, 1, 3, s, fn))) return rc;
     if ((rc = launch_bwd<MODE_TRAIN>(grid, a, s, fn))) return rc;
     return mark_event(ev, 3, s, fn);

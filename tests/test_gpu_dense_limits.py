@@ -8,7 +8,7 @@ import torch
 import synth
 from oracle import oracle as O
 from paper_2112_05131_amd import binding as B
-from tests.gpu_util import RGB_ATOL, make_pair, say
+from tests.gpu_util import RGB_ATOL, assert_grads_close, assert_touched_equal, grad_mass, make_pair, say
 from tests.test_gpu_march import _pose, _render, _view
 
 pytestmark = pytest.mark.gpu
@@ -95,3 +95,46 @@ def test_views_of_opaque_voxels_match_oracle(value, w, h):
     sel = np.sort(np.random.default_rng(6).choice(w * h, min(3000, w * h), replace=False))
     ref = O.render_fwd(og, o[sel], d[sel])[0]
     assert np.abs(got[torch.from_numpy(sel).cuda()].cpu().double().numpy() - ref).max() <= RGB_ATOL
+
+
+@pytest.mark.parametrize("sh_dtype", [B.PLX_F32, B.PLX_F16])
+@pytest.mark.parametrize("value", [float("inf"), 1e30, 1e12])
+@pytest.mark.parametrize("n,cap", [(700, 512), (700, 5), (98400, 512)])
+def test_gradients_before_opaque_voxels(sh_dtype, value, n, cap):
+    """In ray order: the gradients are those of the same grid with densities
+    of 1e12, beyond which nothing changes (no light passes either); the samples
+    before an opaque one keep their transmittance.  With the stated bounds;
+    with per-ray depths and the beta prior's factor unchanged as well."""
+    say("opaque voxels: gradients", sh_dtype, value, n, cap)
+    og, gg = _opaque_pair(sh_dtype, value)
+    og.density[og.density >= 1e12] = 1e12
+    o, d = synth.random_rays(n, seed=96)
+    on, dn = o.numpy(), d.numpy()
+    oc, dc, desc, m = o.cuda(), d.cuda(), gg.desc(), gg.n_vox
+    G = np.random.default_rng(97).normal(size=(n, 3)) * 1e-2
+    Gc = torch.from_numpy(G).float().cuda()
+    Gd = Gc.cpu().double().numpy()
+    ref, tau_ref = O.render_fwd(og, on, dn)[:2]
+    work = B.make_ray_work(n, cap=cap)
+    rgb, tau = torch.empty(n, 3, device="cuda"), torch.empty(n, device="cuda")
+    B.plx_render_fwd_rays(desc, oc, dc, rgb, tau, work)
+    assert np.abs(rgb.cpu().double().numpy() - ref).max() <= RGB_ATOL
+    plain = torch.empty(n, device="cuda")
+    B.plx_render_fwd_rays(desc, oc, dc, rgb, plain)
+    assert torch.equal(tau > 1e9, plain > 1e9) and torch.equal(torch.isinf(tau), torch.isinf(plain))
+    fin = torch.isfinite(plain)
+    assert torch.all((tau[fin] - plain[fin]).abs() <= 1e-6 * (1.0 + plain[fin]))
+    gd, gs, t_ref = O.render_bwd(og, on, dn, Gd)
+    mass = grad_mass(og, on, dn, Gd)
+    grad = torch.zeros(m, 32, device="cuda")
+    touched = torch.zeros(m, dtype=torch.uint8, device="cuda")
+    pl = torch.zeros(2, dtype=torch.float64, device="cuda")
+    B.plx_render_bwd_rays(desc, oc, dc, Gc, work, grad, touched)
+    assert_touched_equal(touched, t_ref, "opaque")
+    assert_grads_close(grad, gd, gs, "opaque", mass)
+    # the beta prior alone: an opaque ray has the largest loss and no gradient
+    grad.zero_()
+    B.plx_render_bwd_rays(desc, oc, dc, torch.zeros_like(Gc), work, grad, touched, priors=B.Priors(0.0, 0.05, 1e-3, pl))
+    _, lb_ref, gd_p, _ = O.regularisers(og, on, dn, 0.0, 0.05, 1e-3)
+    assert abs(pl[1].item() - lb_ref) <= 1e-6 * abs(lb_ref) + 1e-9
+    assert np.all(np.isfinite(gd_p)) and torch.isfinite(grad).all()
