@@ -577,9 +577,16 @@ typedef struct plx_view {
     int32_t width;
     int32_t height;
     int32_t scene;      /* index into the scene table */
-    int32_t reserved;   /* set to 0 */
+    int32_t reserved;   /* 0 or PLX_VIEW_LANE */
     int64_t out_offset; /* index (in pixels) of this view's first pixel in rgb_out */
 } plx_view;
+
+/* plx_view.reserved: march the view's rays by one lane each, rather than by
+ * several.  The faster way for large views whose pixels lie close together in
+ * the scene (from 131,072 pixels, less than 0.2 voxel apart with FP32 records,
+ * 0.1 with 16-bit ones); the same samples and terms, the order of FP32 additions
+ * may differ. */
+#define PLX_VIEW_LANE 1
 
 /* Scene table: the device copy of the descriptors of n_scenes resident scenes
  * (one sh_dtype, occupancy built) that plx_render_views renders from.  Its
@@ -593,8 +600,7 @@ int plx_scene_table_set(const plx_grid *scenes, int32_t n_scenes, void *table, i
 
 /* Bytes of the queue buffer of plx_render_views: device memory, 256-byte
  * aligned, zero-filled once before its first use.  It holds the sticky status
- * word of the launches that were given it, and the tile counter of the one
- * that runs. */
+ * word of the launches that were given it. */
 #define PLX_VIEWS_QUEUE_BYTES 256
 
 /* Renders a batch of novel views of resident scenes (the forward model of

@@ -2320,33 +2320,7 @@ inline int view_lanes(const plx_view &v) {
     return n < (1 << 16) ? 16 : (n < (3 << 18) ? 8 : 4);
 }
 
-// Views from this many pixels on may go to views_lane_kernel.
-constexpr int64_t kLanePix = 1 << 17;
-constexpr int kLaneTile = 8;  // pixels of its tiles along x and y
-
-// Whether a view of a scene takes one lane per ray: when the rays of a tile
-// lie so close that its lanes read the same few records, each lane's corners
-// kept from sample to sample cost less than the march's list.  The pixels'
-// pitch at the grid's centre (or at half the grid's extent, from inside), in
-// voxels, tells it for every resolution, occupancy and distance.  March /
-// lane in ms, FP32: pitch 0.32 2.50 / 2.62 (256^3 at 25%), 0.25 3.36 / 3.04
-// (dense 200^3), 0.17 6.46 / 5.55 (dense 128^3), 0.13 21.7 / 16.9 (512^3 at 5%),
-// 0.03 25.2 / 11.2 (dense 128^3); 16 bits: 0.17 3.50 / 4.00 (dense 128^3), 0.11
-// 20.0 / 19.8 (256^3 at 25%), 0.08 9.67 / 8.33 (dense 200^3), 0.03 13.4 / 8.9.
-template <int DT> __device__ __forceinline__ bool by_lane(const plx_view &v, const GridDev &g) {
-    if ((int64_t)v.width * v.height < kLanePix) return false;
-    constexpr double kPitch = DT == PLX_F32 ? 0.2 : 0.1;
-    const int n[3] = {g.nx, g.ny, g.nz};
-    double d2 = 0.0, half = 0.0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const double x = v.c2w[4 * a + 3] * (double)g.scale[a] + (double)g.offset[a] - 0.5 * (n[a] - 1);
-        d2 = d2 + x * x;
-        half = fmax(half, 0.5 * n[a]);
-    }
-    const double reach = kPitch * v.focal;
-    return fmax(d2, half * half) < reach * reach;
-}
+constexpr int kLaneTile = 8;  // pixels of a PLX_VIEW_LANE view's tiles along x and y
 
 // Tiles of a view (host), by its lanes per ray.
 template <class CUT> inline int64_t tiles_of(const plx_view &v) {
@@ -2372,15 +2346,11 @@ constexpr int64_t kSceneTableHead = 256;
 constexpr int kViewsPerLaunch = 24;
 
 // The caller's queue buffer (PLX_VIEWS_QUEUE_BYTES, zero before first use)
-// holds a sticky status word and, for the kernels of one launch, the views
-// that take a lane per ray (bit i: view i) and their next tile.
+// holds a sticky status word; the dispatcher hands out the tiles.
 struct ViewsQueue {
-    unsigned by_lane;
-    unsigned reserved;
-    unsigned next;
+    unsigned reserved[3];
     unsigned status;
 };
-static_assert(kViewsPerLaunch <= 32, "a bit per view");
 
 struct ViewsArgs {
     const SceneTableHeader *table;
@@ -2389,7 +2359,7 @@ struct ViewsArgs {
     int64_t tile_start[kViewsPerLaunch + 1];
     int lanes[kViewsPerLaunch];  // per ray (view_lanes)
     int n_views;
-    ViewsQueue *queue;
+    unsigned *status;
     float bg[3];
     float *rgb_out;
 };
@@ -2481,9 +2451,8 @@ __device__ __forceinline__ void march_lane(const GridDev &g, const RayGeom &r, i
     }
 }
 
-// Novel views, a tile per workgroup (one wave).  SKIP: without the views that
-// views_pick_kernel gave to views_lane_kernel.
-template <int DT, bool SKIP>
+// Novel views, a tile per workgroup (one wave).
+template <int DT>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void views_kernel(ViewsArgs a) {
     constexpr size_t kLds = sizeof(MarchLds<4, ViewsCut<4>::M>);  // the largest of the cuts
@@ -2491,17 +2460,15 @@ void views_kernel(ViewsArgs a) {
     // a table of other scenes' storage type (or not a scene table): nothing
     // is rendered and the status word says so
     const bool ok = a.table->magic == kSceneMagic && a.table->sh_dtype == DT;
-    const unsigned skip = SKIP ? a.queue->by_lane : 0u;
     for (int64_t tile = blockIdx.x; tile < a.tile_start[a.n_views]; tile += gridDim.x) {
         int lo = 0;  // the view of the tile
         for (int i = 1; i < a.n_views; ++i)
             if (a.tile_start[i] <= tile) lo = i;
         const plx_view &v = a.v[lo];
         if (!ok || v.scene >= a.table->n_scenes) {
-            if (threadIdx.x == 0) atomicOr(&a.queue->status, 1u);
+            if (threadIdx.x == 0) atomicOr(a.status, 1u);
             continue;
         }
-        if (SKIP && (skip >> lo & 1u)) continue;
         const GridDev g = uniform_grid(a.scenes[v.scene]);
         const int64_t tl = tile - a.tile_start[lo];
         if (a.lanes[lo] == 16)
@@ -2513,42 +2480,24 @@ void views_kernel(ViewsArgs a) {
     }
 }
 
-// Finds the views of the launch that take a lane per ray (one wave).
-template <int DT> __global__ __launch_bounds__(kWave) void views_pick_kernel(ViewsArgs a) {
-    bool pick = false;
-    if (a.table->magic == kSceneMagic && a.table->sh_dtype == DT && (int)threadIdx.x < a.n_views) {
-        const plx_view &v = a.v[threadIdx.x];
-        pick = v.scene < a.table->n_scenes && by_lane<DT>(v, a.scenes[v.scene]);
-    }
-    const uint64_t m = __ballot(pick);
-    if (threadIdx.x == 0) {
-        a.queue->by_lane = (unsigned)m;
-        a.queue->next = 0u;
-    }
-}
-
-// Views that by_lane picks: a lane per ray, a tile of kLaneTile^2 pixels per
-// wave; a.tile_start counts the tiles of the views that may be such.  As many
-// waves as the chip holds take the tiles in order from the queue: most
-// launches have no such view, and a workgroup per tile, with nothing to do,
-// still has to wait for its place (twelve mixed requests 2.5% slower).
-constexpr unsigned kLaneBlocks = 3072;  // 256 CUs, 4 SIMDs, 3 waves
+// Views with PLX_VIEW_LANE: a lane per ray, a tile of kLaneTile^2 pixels per
+// workgroup (one wave).  A kernel of its own, as the march's 128 registers do
+// not hold both (4 to 5 times slower, spilled), and launched only for such
+// views: waves that find nothing to do still wait for their place behind other
+// streams' launches (p50 of a half-loaded server 1.46 -> 2.11 ms).
 template <int DT>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(3)))
 void views_lane_kernel(ViewsArgs a) {
-    const unsigned mask = a.queue->by_lane;
-    if (mask == 0u) return;
-    const int64_t n_tiles = a.tile_start[a.n_views];
-    for (;;) {
-        unsigned take = 0u;
-        if (threadIdx.x == 0) take = atomicAdd(&a.queue->next, 1u);
-        const int64_t tile = (unsigned)uni((int)take);
-        if (tile >= n_tiles) break;
+    const bool ok = a.table->magic == kSceneMagic && a.table->sh_dtype == DT;
+    for (int64_t tile = blockIdx.x; tile < a.tile_start[a.n_views]; tile += gridDim.x) {
         int lo = 0;  // the view of the tile
         for (int i = 1; i < a.n_views; ++i)
             if (a.tile_start[i] <= tile) lo = i;
         const plx_view &v = a.v[lo];
-        if (!(mask >> lo & 1u)) continue;
+        if (!ok || v.scene >= a.table->n_scenes) {
+            if (threadIdx.x == 0) atomicOr(a.status, 1u);
+            continue;
+        }
         const GridDev g = uniform_grid(a.scenes[v.scene]);
         const int64_t tl = tile - a.tile_start[lo];
         const int tpr = (v.width + kLaneTile - 1) / kLaneTile;
@@ -3307,43 +3256,36 @@ int plx_render_views(const void *scene_table, int32_t n_scenes, int32_t sh_dtype
     ViewsArgs va;
     va.table = static_cast<const SceneTableHeader *>(scene_table);
     va.scenes = reinterpret_cast<const GridDev *>(static_cast<const char *>(scene_table) + kSceneTableHead);
-    va.queue = static_cast<ViewsQueue *>(queue);
+    va.status = &static_cast<ViewsQueue *>(queue)->status;
     va.rgb_out = rgb_out;
     for (int i = 0; i < 3; ++i) va.bg[i] = opts->background[i];
     for (int32_t first = 0; first < n_views; first += kViewsPerLaunch) {
         va.n_views = std::min(kViewsPerLaunch, n_views - first);
-        int64_t tiles = 0;
-        for (int i = 0; i < va.n_views; ++i) {
-            const plx_view &v = views[first + i];
-            va.v[i] = v;
-            va.lanes[i] = view_lanes(v);
-            va.tile_start[i] = tiles;
-            tiles += va.lanes[i] == 16 ? tiles_of<ViewsCut<16>>(v)
-                                       : (va.lanes[i] == 8 ? tiles_of<ViewsCut<8>>(v) : tiles_of<ViewsCut<4>>(v));
-        }
-        va.tile_start[va.n_views] = tiles;
-        const unsigned nblk = (unsigned)std::min(tiles, kViewsMaxBlocks);
-        ViewsArgs vl = va;  // with the tiles of the views that may take a lane per ray
-        tiles = 0;
-        for (int i = 0; i < va.n_views; ++i) {
-            const plx_view &v = va.v[i];
-            vl.tile_start[i] = tiles;
-            if ((int64_t)v.width * v.height >= kLanePix)
-                tiles += (int64_t)((v.width + kLaneTile - 1) / kLaneTile) * ((v.height + kLaneTile - 1) / kLaneTile);
-        }
-        vl.tile_start[va.n_views] = tiles;
-        const unsigned nl = (unsigned)std::min<int64_t>(tiles, kLaneBlocks);
-        PLX_DISPATCH_DT(sh_dtype, DT, {
-            if (tiles > 0) {
-                views_pick_kernel<DT><<<1, kWave, 0, s>>>(va);
-                views_kernel<DT, true><<<nblk, kWave, 0, s>>>(va);
-                views_lane_kernel<DT><<<nl, kWave, 0, s>>>(vl);
-            } else {
-                views_kernel<DT, false><<<nblk, kWave, 0, s>>>(va);
+        // the tiles of the views that take `lane` (or not), none for the others
+        auto tiles_for = [&](bool lane) {
+            int64_t tiles = 0;
+            for (int i = 0; i < va.n_views; ++i) {
+                const plx_view &v = views[first + i];
+                va.v[i] = v;
+                va.lanes[i] = view_lanes(v);
+                va.tile_start[i] = tiles;
+                if (((v.reserved & PLX_VIEW_LANE) != 0) != lane) continue;
+                if (lane) tiles += (int64_t)((v.width + kLaneTile - 1) / kLaneTile) * ((v.height + kLaneTile - 1) / kLaneTile);
+                else tiles += va.lanes[i] == 16 ? tiles_of<ViewsCut<16>>(v)
+                                                : (va.lanes[i] == 8 ? tiles_of<ViewsCut<8>>(v) : tiles_of<ViewsCut<4>>(v));
             }
-        });
-        int rc = check_launch(fn);
-        if (rc) return rc;
+            va.tile_start[va.n_views] = tiles;
+            return (unsigned)std::min(tiles, kViewsMaxBlocks);
+        };
+        int rc;
+        if (const unsigned nb = tiles_for(false)) {
+            PLX_DISPATCH_DT(sh_dtype, DT, views_kernel<DT><<<nb, kWave, 0, s>>>(va));
+            if ((rc = check_launch(fn))) return rc;
+        }
+        if (const unsigned nb = tiles_for(true)) {
+            PLX_DISPATCH_DT(sh_dtype, DT, views_lane_kernel<DT><<<nb, kWave, 0, s>>>(va));
+            if ((rc = check_launch(fn))) return rc;
+        }
     }
     return PLX_OK;
 }
