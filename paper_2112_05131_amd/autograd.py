@@ -1,7 +1,9 @@
 """torch.autograd binding of the renderer: forward = plx_render_fwd, backward
 = plx_render_bwd (reverse replay with recomputed transmittance).  Saved are
-the rays, the per-ray optical depth and, for a batch in ray order, its occupied
-samples' values, else its segment lists."""
+the rays and, for a batch in ray order (plx_render_fwd_rays and
+plx_render_bwd_rays), its rays' values and the first occupied samples of each,
+else its optical depths and segment lists; nothing where no backward can
+follow."""
 from __future__ import annotations
 
 import torch

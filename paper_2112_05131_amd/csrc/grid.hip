@@ -227,9 +227,10 @@ __global__ __launch_bounds__(kScanThreads) void scan_write_kernel(Pred pred, Wri
 }
 
 // Workspace of the grid calls (caller-owned, plx_grid_workspace_bytes): a
-// 256-byte block of counters, then one byte per cell (two bits are used, the
-// occupied and the stored cells of the prune), then the per-block counts and
-// offsets of the compaction scan.
+// 256-byte block of counters, then a byte per cell, where the prune keeps two
+// bits a cell (occupied, stored) and a compaction, which needs none of these,
+// its offsets and counts per block; the size also has the room that the
+// counts and offsets had behind the bytes.
 struct WsLayout {
     int64_t counters, bytes8, scan, bytes;
 };

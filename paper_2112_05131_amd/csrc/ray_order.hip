@@ -139,7 +139,9 @@ __device__ __forceinline__ void forward_rays(const GridDev &g, const RayArgs &a,
     }
 }
 
-// Forward march of 64 / P rays per wave (one wave per workgroup).
+// Forward march of 64 / P rays per wave (one wave per workgroup).  At 128
+// registers the 16-lane instances that record keep 1 to 14 in scratch, those
+// with 64 lanes none.
 template <int DT, int P, int M, int MODE, int REC>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void rays_fwd_kernel(GridDev g, RayArgs a) {
@@ -423,6 +425,9 @@ __device__ __forceinline__ void backward_ray(const GridDev &g, const RayArgs &a,
     }
 }
 
+// 128 registers for four waves on a SIMD: the training pass fits, the backward
+// alone keeps 2 in scratch, and the instances with priors, whose terms are
+// FP64 over the scans, about 50 (168 and 208 bytes a lane).
 template <int DT, int MODE, bool PRI>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void rays_bwd_kernel(GridDev g, RayArgs a) {

@@ -1812,6 +1812,8 @@ struct SegParts {
 constexpr int kStageFloats = kScatterThreads / kWave * kStageRows * kStageStride;
 static_assert(sizeof(SegParts) <= kStageFloats * sizeof(float), "the parts fit the staging rows");
 
+// 128 registers, for two workgroups on a CU, with 23 more in scratch (80 bytes a
+// lane; 27 and 96 with the Cauchy term).
 template <bool CAUCHY>
 __global__ __launch_bounds__(kScatterThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void seg_scatter_kernel(GridDev g, BinArgs a) {
@@ -2451,7 +2453,8 @@ __device__ __forceinline__ void march_lane(const GridDev &g, const RayGeom &r, i
     }
 }
 
-// Novel views, a tile per workgroup (one wave).
+// Novel views, a tile per workgroup (one wave).  128 registers for four waves
+// on a SIMD, with 3 (FP32) to 7 (16-bit) in scratch.
 template <int DT>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void views_kernel(ViewsArgs a) {
