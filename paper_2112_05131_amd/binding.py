@@ -545,10 +545,12 @@ def ray_cap(n_rays: int, g: PlxGrid | None = None) -> int:
     holds, or as a ray of unit direction has on the grid's diagonal."""
     cap = min(RAY_CAP, RAY_SAMP_BYTES // (20 * max(n_rays, 1)))
     # (a grid that the call will refuse has no diagonal)
-    if g is not None and g.step > 0 and all(s > 0 for s in g.scale):
-        steps = math.sqrt(sum(((int(r) - 1) / s) ** 2 for r, s in zip(g.reso, g.scale))) / g.step
-        if steps < cap:
-            cap = int(steps) + 2
+    if g is not None:
+        (nx, ny, nz), (sx, sy, sz), step = g.reso[:], g.scale[:], g.step
+        if min(sx, sy, sz, step) > 0:
+            steps = math.hypot((nx - 1) / sx, (ny - 1) / sy, (nz - 1) / sz) / step
+            if steps < cap:
+                cap = int(steps) + 2
     return max(1, cap)
 
 
